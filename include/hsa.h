@@ -107,7 +107,10 @@ typedef struct hsa_kv_pool {
 const char* hsa_status_string(hsa_status_t status);
 
 /* Device workspace, in bytes, each call needs for the given sizes. The
- * workspace pointer must be 256-byte aligned. Returns 0 on invalid input. */
+ * workspace pointer must be 256-byte aligned. Returns 0 on invalid input.
+ * For fp32 the size counts scratch that lets the attention cut long items into
+ * pieces; a call whose workspace ends before that scratch (or inside it) runs
+ * with fewer pieces, or none. */
 size_t hsa_state_update_workspace_size(const hsa_config_t* cfg, int32_t n_pages);
 size_t hsa_page_select_workspace_size(const hsa_config_t* cfg, int32_t n_q);
 size_t hsa_sparse_attn_workspace_size(const hsa_config_t* cfg, int32_t n_q,

@@ -163,6 +163,11 @@ size_t partial_ws_bytes(const hsa_config_t* c, int n_q) {
   return attention_partial_bytes(c->batch, c->num_heads, c->head_dim, n_q, kPartPerHead * c->num_heads);
 }
 
+// What the forward call must have: [query sums][selection][split partials].
+size_t forward_need(const hsa_config_t* c, int n_q, int k_max) {
+  return select_ws_bytes(c, n_q) + sel_ws_bytes(c, k_max) + partial_ws_bytes(c, n_q);
+}
+
 // Split partials of a planned launch: the schedule's p.sc.n_part slots (at
 // most kPartPerHead * H, what partial_ws_bytes provides for), then the LSE
 // partials, then the arrival counters of the split query tiles.
@@ -178,6 +183,41 @@ void set_partials(AttnParams& p, const hsa_config_t* c, int n_q, void* base) {
 size_t planned_partial_bytes(const AttnParams& p, const hsa_config_t* c, int n_q) {
   if (c->dtype != HSA_DTYPE_BF16 || p.sc.n_part == 0) return 0;
   return attention_partial_bytes(c->batch, c->num_heads, c->head_dim, n_q, p.sc.n_part);
+}
+
+// The fp32 attention's partials are optional: they come after everything a
+// call needs, the size queries count them, and a call whose workspace ends
+// before them (or inside them) cuts its items into fewer pieces, or none.
+size_t f32_ws_bytes(const hsa_config_t* c, int n_q) {
+  if (c->dtype != HSA_DTYPE_F32) return 0;
+  return attention_f32_partial_bytes(c->batch, c->num_heads, c->head_dim, n_q);
+}
+
+struct Scratch {
+  void* base = nullptr;
+  size_t bytes = 0;
+};
+
+// What is left of a workspace after the `need` bytes of the call.
+Scratch f32_scratch(void* ws, size_t ws_bytes, size_t need) {
+  if (!ws || ws_bytes <= need || reinterpret_cast<uintptr_t>(ws) % kAlign) return Scratch{};
+  return Scratch{static_cast<uint8_t*>(ws) + need, ws_bytes - need};
+}
+
+// The attention launch of a planned call: bf16 with its split partials set,
+// fp32 planned here for the scratch it was given.
+hsa_status_t run_attention(const hsa_config_t* c, int n_q, const int* list_len, AttnParams& p,
+                           void* partials, const Scratch& f32, hipStream_t s) {
+  hipError_t e;
+  if (c->dtype == HSA_DTYPE_BF16) {
+    set_partials(p, c, n_q, partials);
+    e = launch_attention_bf16(c->head_dim, c->batch, p, s);
+  } else {
+    plan_attention_f32(p, c->batch, c->num_heads, c->head_dim, n_q, p.P, list_len, f32.bytes);
+    set_partials_f32(p, c->head_dim, f32.base);
+    e = launch_attention_f32(c->head_dim, c->batch, p, s);
+  }
+  return e == hipSuccess ? HSA_OK : HSA_ERR_DEVICE;
 }
 
 hsa_status_t from_hip(hipError_t e) { return e == hipSuccess ? HSA_OK : HSA_ERR_DEVICE; }
@@ -407,8 +447,8 @@ hsa_status_t check_sparse(const hsa_config_t* cfg, const void* q, int32_t n_q,
 hsa_status_t run_sparse(const hsa_config_t* cfg, const void* q, int32_t n_q,
                         const hsa_kv_pool_t* pool, const int32_t* sel, int32_t k_max,
                         const int32_t* k_h, int32_t cur_first_page, int32_t n_cur_pages,
-                        float* o_sp, float* lse, void* partials, const AdaptiveWs* w,
-                        hipStream_t s) {
+                        float* o_sp, float* lse, void* partials, const Scratch& f32,
+                        const AdaptiveWs* w, hipStream_t s) {
   AttnParams p{};
   p.q = q;
   p.k = pool->k;
@@ -434,9 +474,8 @@ hsa_status_t run_sparse(const hsa_config_t* cfg, const void* q, int32_t n_q,
   if (!plan_attention(p, cfg->batch, cfg->num_heads, cfg->head_dim, n_q, cfg->page_size, list_len,
                       kPartPerHead * cfg->num_heads, cfg->dtype == HSA_DTYPE_BF16, w ? 4 : kPageWaves))
     return HSA_ERR_UNSUPPORTED;
-  if (cfg->dtype == HSA_DTYPE_BF16) set_partials(p, cfg, n_q, partials);
   if (w) set_block_lists(p, *w, static_cast<uint8_t*>(partials) - w->part_off);
-  return from_hip(launch_attention(cfg->dtype, cfg->head_dim, cfg->batch, p, s));
+  return run_attention(cfg, n_q, list_len, p, partials, f32, s);
 }
 
 }  // namespace
@@ -470,13 +509,13 @@ size_t hsa_page_select_workspace_size(const hsa_config_t* cfg, int32_t n_q) {
 size_t hsa_sparse_attn_workspace_size(const hsa_config_t* cfg, int32_t n_q, int32_t k_max,
                                       int32_t n_cur_pages) {
   if (check_cfg(cfg) != HSA_OK || n_q < 1 || k_max < 0 || n_cur_pages < 0) return 0;
-  return partial_ws_bytes(cfg, n_q);
+  return partial_ws_bytes(cfg, n_q) + f32_ws_bytes(cfg, n_q);
 }
 
 size_t hsa_forward_workspace_size(const hsa_config_t* cfg, int32_t n_q, int32_t k_max,
                                   int32_t n_cur_pages) {
   if (check_cfg(cfg) != HSA_OK || n_q < 1 || k_max < 0 || n_cur_pages < 0) return 0;
-  return select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max) + partial_ws_bytes(cfg, n_q);
+  return forward_need(cfg, n_q, k_max) + f32_ws_bytes(cfg, n_q);
 }
 
 hsa_status_t hsa_state_update(const hsa_config_t* cfg, const hsa_kv_pool_t* pool,
@@ -593,14 +632,14 @@ hsa_status_t hsa_sparse_attn(const hsa_config_t* cfg, const void* q, int32_t n_q
   if ((st = validate_pages(cfg, pool, cur_first_page, n_cur_pages, s)) != HSA_OK) return st;
   if ((st = validate_selection(cfg, pool, sel, k_max, s)) != HSA_OK) return st;
   return run_sparse(cfg, q, n_q, pool, sel, k_max, k_h, cur_first_page, n_cur_pages, o_sp, lse, ws,
-                    nullptr, s);
+                    f32_scratch(ws, ws_bytes, partial_ws_bytes(cfg, n_q)), nullptr, s);
 }
 
 size_t hsa_adaptive_workspace_size(const hsa_config_t* cfg, int32_t n_q, int32_t k_max,
                                    int32_t n_cur_pages) {
   if (check_cfg(cfg) != HSA_OK || n_q < 1 || k_max < 0 || n_cur_pages < 0) return 0;
   if ((long)k_max + n_cur_pages > HSA_MAX_LIST) return 0;
-  return adaptive_ws(cfg, n_q, k_max, n_cur_pages).total;
+  return adaptive_ws(cfg, n_q, k_max, n_cur_pages).total + f32_ws_bytes(cfg, n_q);
 }
 
 hsa_status_t hsa_attention_plan(const hsa_config_t* cfg, int32_t n_q, const int32_t* list_len,
@@ -683,7 +722,7 @@ hsa_status_t hsa_sparse_attn_adaptive(const hsa_config_t* cfg, const void* q, in
                         tau_max, w, base, false, BlockSelOut(), s);
   if (st != HSA_OK) return st;
   return run_sparse(cfg, q, n_q, pool, sel, k_max, k_h, cur_first_page, n_cur_pages, o_sp, lse,
-                    base + w.part_off, &w, s);
+                    base + w.part_off, f32_scratch(ws, ws_bytes, w.total), &w, s);
 }
 
 }  // extern "C"
@@ -714,8 +753,7 @@ hsa_status_t check_forward(const hsa_config_t* cfg, const void* q, int32_t n_q,
 // Schedule of the attention launch of the forward calls: each head's list
 // is its selected pages (at most n_cand) plus the current pages.
 bool plan_attend(AttnParams& p, const hsa_config_t* cfg, int n_q, const int32_t* k_h, int n_cand,
-                 int n_cur_pages, bool tile_lists) {
-  int list_len[HSA_MAX_HEADS];
+                 int n_cur_pages, bool tile_lists, int (&list_len)[HSA_MAX_HEADS]) {
   for (int h = 0; h < cfg->num_heads; ++h) list_len[h] = std::min(k_h[h], n_cand) + n_cur_pages;
   return plan_attention(p, cfg->batch, cfg->num_heads, cfg->head_dim, n_q, cfg->page_size, list_len,
                         kPartPerHead * cfg->num_heads, cfg->dtype == HSA_DTYPE_BF16,
@@ -727,7 +765,7 @@ hsa_status_t run_attend(const hsa_config_t* cfg, const void* q, int32_t n_q,
                         const hsa_kv_pool_t* pool, const int32_t* sel, int32_t k_max,
                         const int32_t* k_h, int32_t n_cand, int32_t n_cur_pages,
                         const float* kv_state, const float* k_state, const float* g_lin,
-                        const float* g_sp, void* o, void* partials, hipStream_t s,
+                        const float* g_sp, void* o, void* partials, const Scratch& f32, hipStream_t s,
                         const AdaptiveWs* w = nullptr, uint8_t* wbase = nullptr,
                         const float* o_lin = nullptr) {
   AttnParams p{};
@@ -754,10 +792,10 @@ hsa_status_t run_attend(const hsa_config_t* cfg, const void* q, int32_t n_q,
   p.g_sp = g_sp;
   p.gate_elem = cfg->gate_dims > 1;
   p.o = o;
-  if (!plan_attend(p, cfg, n_q, k_h, n_cand, n_cur_pages, w != nullptr)) return HSA_ERR_UNSUPPORTED;
-  if (cfg->dtype == HSA_DTYPE_BF16) set_partials(p, cfg, n_q, partials);
+  int list_len[HSA_MAX_HEADS];
+  if (!plan_attend(p, cfg, n_q, k_h, n_cand, n_cur_pages, w != nullptr, list_len)) return HSA_ERR_UNSUPPORTED;
   if (w) set_block_lists(p, *w, wbase);
-  return from_hip(launch_attention(cfg->dtype, cfg->head_dim, cfg->batch, p, s));
+  return run_attention(cfg, n_q, list_len, p, partials, f32, s);
 }
 
 // hsa_forward after its checks: page selection into sel_out (or the
@@ -768,14 +806,14 @@ hsa_status_t forward_body(const hsa_config_t* cfg, const void* q, int32_t n_q,
                           const int32_t* k_h, int32_t k_max, const float* kv_state,
                           const float* k_state, const double* page_kmean, const float* g_lin,
                           const float* g_sp, void* o, int32_t* sel_out, uint8_t* base,
-                          hipStream_t s) {
+                          const Scratch& f32, hipStream_t s) {
   int32_t* sel = sel_out ? sel_out : reinterpret_cast<int32_t*>(base + select_ws_bytes(cfg, n_q));
   void* partials = base + select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max);
   hsa_status_t st =
       run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, base, s);
   if (st != HSA_OK) return st;
   return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, partials, s);
+                    g_lin, g_sp, o, partials, f32, s);
 }
 
 }  // namespace
@@ -792,12 +830,13 @@ hsa_status_t hsa_forward(const hsa_config_t* cfg, const void* q, int32_t n_q,
                                   k_state, o);
   if (st != HSA_OK) return st;
   if (!page_kmean) return HSA_ERR_INVALID_ARG;
-  const size_t need = hsa_forward_workspace_size(cfg, n_q, k_max, n_cur_pages);
+  const size_t need = forward_need(cfg, n_q, k_max);
   if ((st = check_ws(ws, ws_bytes, need)) != HSA_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_pages(cfg, pool, 0, n_cand + n_cur_pages, s)) != HSA_OK) return st;
   return forward_body(cfg, q, n_q, pool, n_cand, n_cur_pages, k_h, k_max, kv_state, k_state,
-                      page_kmean, g_lin, g_sp, o, sel_out, static_cast<uint8_t*>(ws), s);
+                      page_kmean, g_lin, g_sp, o, sel_out, static_cast<uint8_t*>(ws),
+                      f32_scratch(ws, ws_bytes, need), s);
 }
 
 hsa_status_t hsa_forward_selected(const hsa_config_t* cfg, const void* q, int32_t n_q,
@@ -810,7 +849,7 @@ hsa_status_t hsa_forward_selected(const hsa_config_t* cfg, const void* q, int32_
                                   k_state, o);
   if (st != HSA_OK) return st;
   if (!sel) return HSA_ERR_INVALID_ARG;
-  const size_t need = hsa_forward_workspace_size(cfg, n_q, k_max, n_cur_pages);
+  const size_t need = forward_need(cfg, n_q, k_max);
   if ((st = check_ws(ws, ws_bytes, need)) != HSA_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_pages(cfg, pool, n_cand, n_cur_pages, s)) != HSA_OK) return st;
@@ -818,7 +857,7 @@ hsa_status_t hsa_forward_selected(const hsa_config_t* cfg, const void* q, int32_
   uint8_t* base = static_cast<uint8_t*>(ws);
   void* partials = base + select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max);
   return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, partials, s);
+                    g_lin, g_sp, o, partials, f32_scratch(ws, ws_bytes, need), s);
 }
 
 hsa_status_t hsa_forward_adaptive(const hsa_config_t* cfg, const void* q, int32_t n_q,
@@ -845,7 +884,7 @@ hsa_status_t hsa_forward_adaptive(const hsa_config_t* cfg, const void* q, int32_
                         base, true, BlockSelOut(), s);
   if (st != HSA_OK) return st;
   return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, base + w.part_off, s, &w, base);
+                    g_lin, g_sp, o, base + w.part_off, f32_scratch(ws, ws_bytes, w.total), s, &w, base);
 }
 
 hsa_status_t hsa_chunk_select(const hsa_config_t* cfg, const float* prompt_emb,
@@ -889,8 +928,9 @@ hsa_status_t hsa_forward_retrieval(const hsa_config_t* cfg, const void* q, int32
   if (st != HSA_OK) return st;
   if (!page_kmean || !prompt_emb || !chunk_emb || !chunk_first) return HSA_ERR_INVALID_ARG;
   if (emb_dim < 1 || n_chunks < 1) return HSA_ERR_INVALID_ARG;
-  const size_t fwd = hsa_forward_workspace_size(cfg, n_q, k_max, n_cur_pages);
-  if ((st = check_ws(ws, ws_bytes, fwd + align_up((size_t)cfg->batch * 2 * 4))) != HSA_OK) return st;
+  const size_t fwd = forward_need(cfg, n_q, k_max);
+  const size_t need = fwd + align_up((size_t)cfg->batch * 2 * 4);
+  if ((st = check_ws(ws, ws_bytes, need)) != HSA_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_pages(cfg, pool, 0, n_cand + n_cur_pages, s)) != HSA_OK) return st;
   uint8_t* base = static_cast<uint8_t*>(ws);
@@ -904,7 +944,7 @@ hsa_status_t hsa_forward_retrieval(const hsa_config_t* cfg, const void* q, int32
                   range);
   if (st != HSA_OK) return st;
   return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, partials, s);
+                    g_lin, g_sp, o, partials, f32_scratch(ws, ws_bytes, need), s);
 }
 
 size_t hsa_linformer_compress_workspace_size(const hsa_config_t* cfg, int32_t rank,
@@ -971,7 +1011,9 @@ hsa_status_t hsa_forward_linformer(const hsa_config_t* cfg, const void* q, int32
   if (!valid_rank(rank)) return HSA_ERR_UNSUPPORTED;
   if ((st = check_adaptive(cfg, n_q, k_max, n_cur_pages, tau_min, tau_max)) != HSA_OK) return st;
   const AdaptiveWs w = adaptive_ws(cfg, n_q, k_max, n_cur_pages);
-  if ((st = check_ws(ws, ws_bytes, w.total + o_lin_bytes(cfg, n_q))) != HSA_OK) return st;
+  const size_t need = w.total + o_lin_bytes(cfg, n_q);
+  if ((st = check_ws(ws, ws_bytes, need)) != HSA_OK) return st;
+  const Scratch f32 = f32_scratch(ws, ws_bytes, need);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_pages(cfg, pool, 0, n_cand + n_cur_pages, s)) != HSA_OK) return st;
   uint8_t* base = static_cast<uint8_t*>(ws);
@@ -988,10 +1030,10 @@ hsa_status_t hsa_forward_linformer(const hsa_config_t* cfg, const void* q, int32
   cr.page_size = rank;
   const hsa_kv_pool_t cpool{ck, cv, pool->page_table, pool->num_slots, pool->max_pages};
   st = run_sparse(&cr, q, n_q, &cpool, sel, k_max, k_h, n_cand, n_cur_pages, o_lin, nullptr,
-                  base + w.part_off, nullptr, s);
+                  base + w.part_off, f32, nullptr, s);
   if (st != HSA_OK) return st;
   return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, nullptr, nullptr,
-                    g_lin, g_sp, o, base + w.part_off, s, &w, base, o_lin);
+                    g_lin, g_sp, o, base + w.part_off, f32, s, &w, base, o_lin);
 }
 
 }  // extern "C"
@@ -1036,8 +1078,13 @@ size_t hsa_forward_noalloc_bytes(const hsa_config_t* cfg, int32_t n_q, int32_t n
     return 0;
   if (check_budgets(cfg, k_h, k_max) != HSA_OK) return 0;
   AttnParams p{};
-  if (!plan_attend(p, cfg, n_q, k_h, n_cand, n_cur_pages, false)) return 0;
-  return select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max) + planned_partial_bytes(p, cfg, n_q);
+  int list_len[HSA_MAX_HEADS];
+  if (!plan_attend(p, cfg, n_q, k_h, n_cand, n_cur_pages, false, list_len)) return 0;
+  const size_t need =
+      select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max) + planned_partial_bytes(p, cfg, n_q);
+  if (cfg->dtype != HSA_DTYPE_F32 || need >= (size_t)HSA_NOALLOC_SCRATCH_BYTES) return need;
+  return need + plan_attention_f32(p, cfg->batch, cfg->num_heads, cfg->head_dim, n_q, cfg->page_size,
+                                   list_len, (size_t)HSA_NOALLOC_SCRATCH_BYTES - need);
 }
 
 hsa_status_t hsa_forward_noalloc(const hsa_config_t* cfg, const void* q, int32_t n_q,
@@ -1058,7 +1105,8 @@ hsa_status_t hsa_forward_noalloc(const hsa_config_t* cfg, const void* q, int32_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = validate_pages(cfg, pool, 0, n_cand + n_cur_pages, s)) != HSA_OK) return st;
   return forward_body(cfg, q, n_q, pool, n_cand, n_cur_pages, k_h, k_max, kv_state, k_state,
-                      page_kmean, g_lin, g_sp, o, sel_out, base, s);
+                      page_kmean, g_lin, g_sp, o, sel_out, base,
+                      f32_scratch(base, HSA_NOALLOC_SCRATCH_BYTES, forward_need(cfg, n_q, k_max)), s);
 }
 
 }  // extern "C"

@@ -1060,132 +1060,6 @@ __global__ __launch_bounds__(512, 1) void attn_pp_kernel(AttnParams p_arg) {
   }  // segments
 }
 
-// fp32 inputs: VALU attention, 64 queries per workgroup, 4 lanes per query.
-// Page mode walks the selected pages and then the current pages; list mode
-// walks the 64-key tiles its query block keeps (one query block per
-// workgroup: query tile qtile / 2, mask bit qtile % 2 of the tile lists).
-template <int D, bool kList>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnParams p) {
-  constexpr int T = 32, BM = 64, DP = D / 4;
-  __shared__ float ks[T][D + 1];
-  __shared__ float vs[T][D + 1];
-  __shared__ float qs[BM][D + 1];
-  __shared__ int32_t slots[HSA_MAX_LIST];
-  const int tid = threadIdx.x, qr = tid >> 2, part = tid & 3;
-  const int qtile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int H = p.H, P = p.P;
-  const float* qg = static_cast<const float*>(p.q);
-  const float* kg = static_cast<const float*>(p.k);
-  const float* vg = static_cast<const float*>(p.v);
-  const int q0 = qtile * BM;
-  for (int x = tid; x < BM * D; x += 256) {
-    const int r = x / D, dd = x % D;
-    const int qi = min(q0 + r, p.n_q - 1);
-    qs[r][dd] = qg[(((size_t)b * p.n_q + qi) * H + h) * D + dd];
-  }
-  float acc[DP];
-  for (int e = 0; e < DP; ++e) acc[e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  // keys [off0, off0 + nk) of the page at (slot * H + h) = ph, nk <= T
-  auto step = [&](size_t ph, int off0, int nk) {
-    __syncthreads();
-    const float* kp = kg + ph * P * D;
-    const float* vp = vg + ph * D * P;
-    for (int x = tid; x < T * D; x += 256) {
-      const int key = x / D, dd = x % D;
-      ks[key][dd] = key < nk ? kp[(size_t)(off0 + key) * D + dd] : 0.f;
-    }
-    for (int x = tid; x < T * D; x += 256) {
-      const int dd = x / T, key = x % T;
-      vs[key][dd] = key < nk ? vp[(size_t)dd * P + off0 + key] : 0.f;
-    }
-    __syncthreads();
-    float sc[T];
-    float mx = -INFINITY;
-    for (int key = 0; key < T; ++key) {
-      float s = 0.f;
-      for (int e = 0; e < DP; ++e) s = fmaf(qs[qr][part * DP + e], ks[key][part * DP + e], s);
-      s += __shfl_xor(s, 1);
-      s += __shfl_xor(s, 2);
-      s = key < nk ? s * p.sm_scale : -INFINITY;
-      sc[key] = s;
-      mx = fmaxf(mx, s);
-    }
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = expf(m_run - m_new);
-    l_run *= alpha;
-    for (int e = 0; e < DP; ++e) acc[e] *= alpha;
-    for (int key = 0; key < nk; ++key) {
-      const float pk = expf(sc[key] - m_new);
-      l_run += pk;
-      for (int e = 0; e < DP; ++e) acc[e] = fmaf(pk, vs[key][part * DP + e], acc[e]);
-    }
-    m_run = m_new;
-  };
-  if constexpr (kList) {
-    const size_t cell = ((size_t)b * H + h) * p.sc.nqt + qtile / 2;
-    const int len = p.blist_len[cell], bit = qtile & 1;
-    const int2* lst = p.blist + cell * p.blist_cap;
-    for (int u = 0; u < len; ++u) {
-      const int2 e = lst[u];
-      if (!((e.y >> bit) & 1)) continue;
-      const int k0 = (e.y >> 2) * 64, k1 = min(P, k0 + 64);
-      for (int off = k0; off < k1; off += T) step((size_t)e.x, off, min(T, k1 - off));
-    }
-  } else {
-    const int32_t* selrow = p.sel + ((size_t)b * H + h) * p.k_max;
-    int n_sel = 0;
-    while (n_sel < p.k_max) {
-      const int e = selrow[n_sel];
-      if (e < 0 || e >= p.max_pages) break;
-      ++n_sel;
-    }
-    const int n_list = n_sel + p.n_cur;
-    for (int i = tid; i < n_list; i += 256) {
-      const int lp = i < n_sel ? selrow[i] : p.cur_first + (i - n_sel);
-      slots[i] = clampi(p.page_table[(size_t)b * p.max_pages + lp], 0, p.num_slots - 1);
-    }
-    __syncthreads();
-    for (int li = 0; li < n_list; ++li)
-      for (int off = 0; off < P; off += T) step((size_t)slots[li] * H + h, off, min(T, P - off));
-  }
-  __syncthreads();  // the query rows are complete even if no key was visited
-  const int qi = q0 + qr;
-  if (qi >= p.n_q) return;
-  const float inv_l = l_run > 0.f ? 1.f / l_run : 0.f;
-  if (p.mode == ATTN_SPARSE) {
-    float* orow = p.o_sp + (((size_t)b * p.n_q + qi) * H + h) * D + part * DP;
-    for (int e = 0; e < DP; ++e) orow[e] = acc[e] * inv_l;
-    if (p.lse && part == 0)
-      p.lse[((size_t)b * H + h) * p.n_q + qi] = l_run > 0.f ? m_run + logf(l_run) : -INFINITY;
-    return;
-  }
-  const size_t gi = ((size_t)b * p.n_q + qi) * H + h;
-  // gate weights of element e of this thread's part of the row
-  auto sig = [](const float* g, size_t i) { return g ? 1.f / (1.f + expf(-g[i])) : 0.5f; };
-  const float wl_h = p.gate_elem ? 0.f : sig(p.g_lin, gi);
-  const float wsp_h = p.gate_elem ? 0.f : sig(p.g_sp, gi);
-  auto wl = [&](int e) { return p.gate_elem ? sig(p.g_lin, gi * D + part * DP + e) : wl_h; };
-  auto wsp = [&](int e) { return p.gate_elem ? sig(p.g_sp, gi * D + part * DP + e) : wsp_h; };
-  float* orow = static_cast<float*>(p.o) + gi * D + part * DP;
-  if (p.o_lin) {
-    // linear branch from another launch (Linformer): gated sum only
-    const float* lrow = p.o_lin + gi * D + part * DP;
-    for (int e = 0; e < DP; ++e) orow[e] = wl(e) * lrow[e] + wsp(e) * acc[e] * inv_l;
-    return;
-  }
-  const float* st = p.kv_state + ((size_t)b * H + h) * D * D;
-  const float* zz = p.k_state + ((size_t)b * H + h) * D;
-  float den = 0.f;
-  for (int i = 0; i < D; ++i) den = fmaf(phi(qs[qr][i]), zz[i], den);
-  for (int e = 0; e < DP; ++e) {
-    const int j = part * DP + e;
-    float num = 0.f;
-    for (int i = 0; i < D; ++i) num = fmaf(phi(qs[qr][i]), st[(size_t)j * D + i], num);
-    orow[e] = wl(e) * (num / den) + wsp(e) * acc[e] * inv_l;
-  }
-}
-
 }  // namespace
 
 // Partials are kept per 32-query wave slot; the widest workgroup pads the
@@ -1548,45 +1422,34 @@ bool plan_schedule(AttnParams& p, int H, int d, int n_q, int P, const int* list_
 
 }  // namespace
 
-hipError_t launch_attention(int dtype, int d, int B, const AttnParams& p, hipStream_t s) {
-  if (dtype == HSA_DTYPE_BF16) {
-    if (p.sc.n_chead > 0) {
-      // arrival counters of the split tiles (a fill kernel, not a memset, so
-      // that the launch sequence can be captured into a graph)
-      const int n = B * p.H * p.sc.nqt;
-      zero_counters_kernel<<<(n + 255) / 256, 256, 0, s>>>(p.attn_ctr, n);
-    }
-    const bool small = p.P < kBN, list = p.blist != nullptr;
-    // tile lists (block-sparse mode) are built per 128-query tile and walked
-    // by 4-wave workgroups; the page walk takes 8-wave ones, one per range
-    if (p.sc.waves != (list ? 4 : 8)) return hipErrorInvalidValue;
-    const dim3 grid = list ? dim3(8 * std::max(1, p.sc.xcd_items), B) : dim3(p.sc.sk_g);
-    if (d == 128) {
-      if (list) {
-        if (small) attn_bf16_kernel<128, true, 4><<<grid, 256, 0, s>>>(p);
-        else attn_bf16_kernel<128, false, 4><<<grid, 256, 0, s>>>(p);
-      } else {
-        if (small) attn_pp_kernel<128, true><<<grid, 512, 0, s>>>(p);
-        else attn_pp_kernel<128, false><<<grid, 512, 0, s>>>(p);
-      }
-    } else {
-      if (list) {
-        if (small) attn_bf16_kernel<64, true, 4><<<grid, 256, 0, s>>>(p);
-        else attn_bf16_kernel<64, false, 4><<<grid, 256, 0, s>>>(p);
-      } else {
-        if (small) attn_pp_kernel<64, true><<<grid, 512, 0, s>>>(p);
-        else attn_pp_kernel<64, false><<<grid, 512, 0, s>>>(p);
-      }
-    }
+// arrival counters of the split tiles (a fill kernel, not a memset, so that
+// the launch sequence can be captured into a graph)
+void zero_counters(int32_t* ctr, int n, hipStream_t s) {
+  zero_counters_kernel<<<(n + 255) / 256, 256, 0, s>>>(ctr, n);
+}
 
-  } else {
-    const dim3 grid((p.n_q + 63) / 64, p.H, B);
-    if (p.blist) {
-      if (d == 128) attn_f32_kernel<128, true><<<grid, 256, 0, s>>>(p);
-      else attn_f32_kernel<64, true><<<grid, 256, 0, s>>>(p);
+hipError_t launch_attention_bf16(int d, int B, const AttnParams& p, hipStream_t s) {
+  if (p.sc.n_chead > 0) zero_counters(p.attn_ctr, B * p.H * p.sc.nqt, s);
+  const bool small = p.P < kBN, list = p.blist != nullptr;
+  // tile lists (block-sparse mode) are built per 128-query tile and walked
+  // by 4-wave workgroups; the page walk takes 8-wave ones, one per range
+  if (p.sc.waves != (list ? 4 : 8)) return hipErrorInvalidValue;
+  const dim3 grid = list ? dim3(8 * std::max(1, p.sc.xcd_items), B) : dim3(p.sc.sk_g);
+  if (d == 128) {
+    if (list) {
+      if (small) attn_bf16_kernel<128, true, 4><<<grid, 256, 0, s>>>(p);
+      else attn_bf16_kernel<128, false, 4><<<grid, 256, 0, s>>>(p);
     } else {
-      if (d == 128) attn_f32_kernel<128, false><<<grid, 256, 0, s>>>(p);
-      else attn_f32_kernel<64, false><<<grid, 256, 0, s>>>(p);
+      if (small) attn_pp_kernel<128, true><<<grid, 512, 0, s>>>(p);
+      else attn_pp_kernel<128, false><<<grid, 512, 0, s>>>(p);
+    }
+  } else {
+    if (list) {
+      if (small) attn_bf16_kernel<64, true, 4><<<grid, 256, 0, s>>>(p);
+      else attn_bf16_kernel<64, false, 4><<<grid, 256, 0, s>>>(p);
+    } else {
+      if (small) attn_pp_kernel<64, true><<<grid, 512, 0, s>>>(p);
+      else attn_pp_kernel<64, false><<<grid, 512, 0, s>>>(p);
     }
   }
   return hipGetLastError();

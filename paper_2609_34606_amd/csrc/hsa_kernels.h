@@ -259,7 +259,21 @@ size_t attention_partial_bytes(int B, int H, int d, int n_q, int n_part);
 size_t attention_partial_o_bytes(int B, int d, int n_q, int n_part);
 size_t attention_partial_lse_bytes(int B, int n_q, int n_part);
 
-hipError_t launch_attention(int dtype, int d, int B, const AttnParams& p,
-                            hipStream_t s);
+hipError_t launch_attention_bf16(int d, int B, const AttnParams& p, hipStream_t s);
+// Zeroes n arrival counters.
+void zero_counters(int32_t* ctr, int n, hipStream_t s);
+
+// fp32 attention. plan_attention_f32 fills p.sc: the steps (64 keys of one 64-query
+// item) of each head's items (sk_head_off, within a batch entry), the equal
+// ranges of all steps, one per workgroup (sk_g, sk_q, sk_rm; an item counts as
+// one step where every workgroup takes a whole one) and whether items are cut
+// (n_chead), with partials of at most avail bytes, and returns the bytes it
+// uses; set_partials_f32 carves them. attention_f32_partial_bytes: what every plan
+// of these sizes can use.
+size_t attention_f32_partial_bytes(int B, int H, int d, int n_q);
+size_t plan_attention_f32(AttnParams& p, int B, int H, int d, int n_q, int P, const int* list_len,
+                          size_t avail);
+void set_partials_f32(AttnParams& p, int d, void* base);
+hipError_t launch_attention_f32(int d, int B, const AttnParams& p, hipStream_t s);
 
 }  // namespace hsa

@@ -1,0 +1,124 @@
+"""fp32 attention at the edges of its tiles, pieces and pointers: 64-query
+blocks, 32-key tiles (the window at a page's end, pages shorter than a tile),
+items cut into pieces or not (by the scratch the workspace leaves), operands
+aligned to 4 bytes only, and infinite values. Against the fp64 oracle with the
+repository's fp32 bar."""
+import numpy as np
+import pytest
+
+from synth_inputs import make_case
+from synth_inputs.configs import Workload
+
+from hsa_testlib import F32_TOL, assert_close, run_oracle, say, to_host, upload
+
+pytestmark = pytest.mark.gpu
+
+BASE = Workload("attn_f32", batch=1, heads=2, head_dim=64, n_q=65, page_size=40, n_cand=5,
+                n_cur=2, k_h=(3, 1), dtype="f32", seed=71, value_scale=0.35, gates=True)
+
+
+def _layer(wl, dev):
+    from paper_2609_34606_amd import HsaLayer
+    import torch
+    layer = HsaLayer(wl.batch, wl.heads, wl.head_dim, wl.page_size, torch.float32, "cuda:0",
+                     k_pool=dev["k_pool"], v_pool=dev["v_pool"], page_table=dev["page_table"])
+    layer.fold(0, wl.n_pages)
+    return layer
+
+
+def _oracle(case, wl):
+    return run_oracle(dict(q=case.q, k_pool=case.k_pool, v_pool=case.v_pool,
+                           page_table=case.page_table, g_lin=case.g_lin, g_sp=case.g_sp), wl,
+                      wl.budgets())
+
+
+@pytest.mark.parametrize("n_q,P,n_cand,n_cur,k_h,d,B", [
+    (1, 8, 3, 1, (2, 0), 64, 1),          # one query, pages shorter than a tile, one-page list
+    (63, 24, 5, 2, (3, 1), 128, 2),       # 24-key pages: every tile clamped
+    (64, 32, 5, 2, (3, 1), 128, 1),       # whole tiles and blocks
+    (65, 40, 5, 2, (3, 1), 128, 3),       # 8-key windows, a block of one query
+    (257, 392, 9, 1, (8, 2), 64, 1),      # pieces of unequal lists
+    (300, 1560, 6, 3, (6, 1), 128, 1)])
+def test_edges_with_full_and_smallest_workspace(n_q, P, n_cand, n_cur, k_h, d, B):
+    import torch
+    from paper_2609_34606_amd import config, hsa_forward, hsa_forward_workspace_size
+    wl = BASE.replace(n_q=n_q, page_size=P, n_cand=n_cand, n_cur=n_cur, k_h=k_h, head_dim=d, batch=B)
+    say(f"[case] f32 attention edges {wl}")
+    case = make_case(wl)
+    dev = upload(case)
+    layer = _layer(wl, dev)
+    ref = _oracle(case, wl)["O"]
+    k_max = max(k_h)
+    full = hsa_forward_workspace_size(layer.cfg, n_q, k_max, n_cur)
+    # the bytes a call needs: the query sums and the selection (a bf16 config
+    # differs by its split partials only), and the pieces' scratch after them
+    need = -(-n_q // 32) * wl.heads * d * 8 * B
+    need = -(-need // 256) * 256 + 256
+    assert full > need
+    for nbytes in (full, need, need + (full - need) // 2):
+        o = torch.full_like(dev["q"], float("nan"))
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+        hsa_forward(layer.cfg, dev["q"], n_q, layer.pool, n_cand, n_cur, list(k_h), k_max,
+                    layer.kv_state, layer.k_state, layer.page_kmean, dev["g_lin"], dev["g_sp"], o, ws=ws)
+        torch.cuda.synchronize()
+        assert_close(f"O ({nbytes} bytes)", to_host(o), ref, **F32_TOL)
+    st = hsa_forward(layer.cfg, dev["q"], n_q, layer.pool, n_cand, n_cur, list(k_h), k_max,
+                     layer.kv_state, layer.k_state, layer.page_kmean, dev["g_lin"], dev["g_sp"], o,
+                     ws=torch.empty(need - 256, dtype=torch.uint8, device="cuda:0"), check=False)
+    assert st == 4  # HSA_ERR_WORKSPACE below what a call needs, as for bf16
+
+
+def test_operands_aligned_to_four_bytes():
+    import torch
+    wl = BASE.replace(n_q=130, page_size=200, head_dim=128, seed=72)
+    say(f"[case] f32 unaligned {wl}")
+    case = make_case(wl)
+    dev = upload(case)
+
+    def shifted(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        v = buf[1:].view(t.shape)
+        v.copy_(t)
+        assert v.data_ptr() % 16 == 4
+        return v
+
+    layer = _layer(wl, dev)
+    layer.k_pool, layer.v_pool = shifted(dev["k_pool"]), shifted(dev["v_pool"])
+    layer.kv_state, layer.k_state = shifted(layer.kv_state), shifted(layer.k_state)
+    out = shifted(torch.zeros_like(dev["q"]))
+    # the query sums of the page selection read 16 bytes at a time: the queries
+    # keep their alignment in hsa_forward, and lose it in the sparse branch
+    layer.forward(dev["q"], wl.n_cand, wl.n_cur, list(wl.budgets()), g_lin=dev["g_lin"],
+                  g_sp=dev["g_sp"], out=out)
+    torch.cuda.synchronize()
+    ref = _oracle(case, wl)
+    assert_close("O", to_host(out), ref["O"], **F32_TOL)
+    from paper_2609_34606_amd import hsa_sparse_attn
+    sel = torch.from_numpy(np.ascontiguousarray(ref["sel"])).to("cuda:0").to(torch.int32)
+    o_sp = shifted(torch.zeros_like(dev["q"]))
+    hsa_sparse_attn(layer.cfg, shifted(dev["q"]), wl.n_q, layer.pool, sel, sel.shape[-1],
+                    list(wl.budgets()), wl.n_cand, wl.n_cur, o_sp)
+    torch.cuda.synchronize()
+    assert_close("O_sp", to_host(o_sp), ref["O_sp"], **F32_TOL)
+
+
+def test_infinite_value_stays_in_its_page_and_dimension():
+    # a value of +inf makes its (head, dimension) infinite and nothing else,
+    # also where a masked window re-reads the key that holds it (page 40: keys
+    # 8..31 are read again by the window of keys 32..39)
+    import torch
+    from paper_2609_34606_amd import hsa_sparse_attn
+    wl = BASE.replace(n_cand=0, k_h=(0, 0), n_cur=2, n_q=20, seed=73)
+    say(f"[case] f32 infinite value {wl}")
+    case = make_case(wl)
+    dev = upload(case)
+    slot = int(case.page_table[0, 1])
+    dev["v_pool"][slot, 1, 5, 20] = float("inf")
+    layer = _layer(wl, dev)
+    o_sp = torch.zeros((1, wl.n_q, wl.heads, wl.head_dim), dtype=torch.float32, device="cuda:0")
+    hsa_sparse_attn(layer.cfg, dev["q"], wl.n_q, layer.pool, None, 0, None, 0, 2, o_sp)
+    torch.cuda.synchronize()
+    got = to_host(o_sp)
+    assert np.isposinf(got[0, :, 1, 5]).all()
+    got[0, :, 1, 5] = 0.0
+    assert np.isfinite(got).all()
