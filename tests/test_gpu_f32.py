@@ -1,5 +1,5 @@
-"""fp32 attention at the edges of its tiles, pieces and pointers: 64-query
-blocks, 32-key tiles (the window at a page's end, pages shorter than a tile),
+"""fp32 attention and state at the edges of their tiles, pieces and pointers:
+64-query blocks, 32-key tiles (the window at a page's end, pages shorter than a tile),
 items cut into pieces or not (by the scratch the workspace leaves), operands
 aligned to 4 bytes only, and infinite values. Against the fp64 oracle with the
 repository's fp32 bar."""
@@ -100,6 +100,45 @@ def test_operands_aligned_to_four_bytes():
                     list(wl.budgets()), wl.n_cand, wl.n_cur, o_sp)
     torch.cuda.synchronize()
     assert_close("O_sp", to_host(o_sp), ref["O_sp"], **F32_TOL)
+
+
+@pytest.mark.parametrize("P,n_pages,H,d,B,shift", [(8, 1, 1, 64, 1, 0), (24, 3, 2, 128, 1, 1),
+                                                    (40, 30, 3, 64, 2, 0), (392, 9, 8, 128, 1, 1),
+                                                    (1560, 3, 1, 128, 1, 0)])
+def test_state_and_index_of_some_pages(P, n_pages, H, d, B, shift):
+    # pages [1, 1 + n_pages) folded on top of a state, the pool aligned to 4
+    # bytes only where shift is 1; 64-bit numpy sums. The state's terms are
+    # fp32 products added in fp32: 1e-5 as in the parity tests.
+    import torch
+    from paper_2609_34606_amd import HsaLayer
+    say(f"[case] f32 state P={P} pages={n_pages} H={H} d={d} B={B} shift={shift}")
+    r = np.random.default_rng(74)
+    slots = B * (n_pages + 2)
+    k = r.standard_normal((slots, H, P, d)).astype(np.float32)
+    v = r.standard_normal((slots, H, d, P)).astype(np.float32)
+    table = r.permutation(slots).reshape(B, n_pages + 2).astype(np.int32)
+
+    def up(a):
+        buf = torch.empty(a.size + shift, dtype=torch.float32, device="cuda:0")
+        t = buf[shift:].view(a.shape)
+        t.copy_(torch.from_numpy(a))
+        return t
+
+    layer = HsaLayer(B, H, d, P, torch.float32, "cuda:0", k_pool=up(k), v_pool=up(v),
+                     page_table=torch.from_numpy(table).to("cuda:0"))
+    layer.kv_state.fill_(0.5)
+    layer.k_state.fill_(0.25)
+    layer.fold(1, n_pages)
+    torch.cuda.synchronize()
+    pages = table[:, 1:1 + n_pages]
+    kk = k[pages].astype(np.float64)                      # [B, n, H, P, d]
+    f = np.where(kk > 0, kk + 1.0, np.exp(np.minimum(kk, 0.0)))
+    S = 0.5 + np.matmul(v[pages].astype(np.float64), f).sum(1)   # [B, H, d(v), d(k)]
+    assert_close("kv_state", to_host(layer.kv_state), S, max_abs=np.inf, rel_l2=1e-5)
+    assert_close("k_state", to_host(layer.k_state), 0.25 + f.sum((1, 3)), max_abs=np.inf, rel_l2=1e-5)
+    mean = to_host(layer.page_kmean)
+    np.testing.assert_allclose(mean[:, :, 1:1 + n_pages], kk.mean(3).swapaxes(1, 2), rtol=1e-12, atol=1e-15)
+    assert (mean[:, :, 0] == 0).all() and (mean[:, :, -1] == 0).all()
 
 
 def test_infinite_value_stays_in_its_page_and_dimension():
