@@ -133,3 +133,37 @@ def test_adaptive_forward_on_cube_ordered_pages_paper_geometry():
                                   g_lin=g_lin, g_sp=g_sp, query_blocks=qbs)
     fr = compare(gpu, ref, wl, wl.k_h, query_blocks=qbs)
     assert min(fr) < 1.0   # the selection keeps a subset of the blocks
+
+
+@pytest.mark.parametrize("P,dtype,d,shift", [(8, "bf16", 64, 0), (72, "bf16", 128, 1), (1560, "bf16", 128, 3),
+                                             (64, "f32", 64, 1), (136, "f32", 128, 0)])
+def test_page_writer_runs_and_alignments(P, dtype, d, shift):
+    # last runs shorter than 64 tokens, and sources and pools that start `shift`
+    # elements past a 16-byte boundary: every byte where it belongs
+    import torch
+    from paper_2609_34606_amd import config, hsa_page_write, kv_pool
+    say(f"[case] page writer P={P} {dtype} d={d} shift={shift}")
+    B, H, n = 2, 3, 2
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(5)
+
+    def tensor(*shape):
+        buf = torch.randn(int(np.prod(shape)) + shift, generator=g, device="cuda:0").to(dt)
+        return buf[shift:].view(shape)
+
+    k_src, v_src = tensor(B, n * P, H, d), tensor(B, n * P, H, d)
+    slots = B * (n + 1)
+    k_pool, v_pool = tensor(slots, H, P, d), tensor(slots, H, d, P)
+    table = torch.randperm(slots, generator=g, device="cuda:0").reshape(B, n + 1).to(torch.int32)
+    src_of = torch.randperm(P, generator=g, device="cuda:0").to(torch.int32)
+    want_k, want_v = k_pool.clone(), v_pool.clone()
+    for b in range(B):
+        for i in range(n):
+            slot = int(table[b, 1 + i])
+            want_k[slot] = k_src[b, i * P:(i + 1) * P][src_of.long()].transpose(0, 1)
+            want_v[slot] = v_src[b, i * P:(i + 1) * P][src_of.long()].permute(1, 2, 0)
+    cfg = config(B, H, d, P, dt)
+    hsa_page_write(cfg, kv_pool(k_pool, v_pool, table, cfg), k_src, v_src, 1, n, src_of=src_of)
+    torch.cuda.synchronize()
+    assert torch.equal(k_pool, want_k) and torch.equal(v_pool, want_v)
