@@ -6,14 +6,24 @@
 // compressed pages form a KV pool of page size r that the attention kernels
 // read like any other pool.
 //
-// bf16: both products contract over the page's tokens. Value pages are
-// stored d-major and the projections rank-major, so their 64-token tiles go
-// straight from HBM into LDS (global_load_lds) as MFMA operands; key rows
-// come through registers and are written to LDS transposed ([d][token]).
-// One workgroup per (page part, head); 32x32x16 bf16 MFMAs with fp32
-// accumulation; waves 0-1 own ck's output tiles, waves 2-3 cv's. A page is
-// split into parts only when there are too few (page, head) pairs to fill
-// the chip; parts write fp32 partials that a second kernel sums in order.
+// bf16: both products contract over the page's tokens, and neither needs the
+// other's operands, so a work item is one product of one (page part, head):
+// 64-token tiles of the projection (rank-major rows) and of the data (value
+// rows as stored; key rows transposed to [d][token] on the way into LDS),
+// 32x32x16 bf16 MFMAs with fp32 accumulation. A page is split into parts only
+// when there are too few (page, head) pairs to fill the chip; parts write fp32
+// partials that a second kernel sums in order.
+//
+// Bound: HBM (the pages; the projections come from L2). Under load a tile
+// takes about 5 us to arrive, so what counts is the bytes in flight per CU:
+// the data of the next two tiles is in registers or on its way while a tile is
+// computed, at four workgroups per CU. Measured, 48 pages of 1560 tokens x 12
+// heads x d128, rank 64 (460 MB): 112 us, 4.3 TB/s counting each page once;
+// one workgroup per page and head with both products, loading a tile and then
+// computing it, took 157 us, the same with one tile prefetched 132 us. Five
+// workgroups per CU spill registers: 140 us.
+#include <type_traits>
+
 #include "hsa_device.h"
 #include "hsa_kernels.h"
 
@@ -29,155 +39,212 @@ __device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 4)) &
 
 template <int D, int R>
 struct CompressSmem {
-  uint8_t kt[D * kRow];  // K^T tile [d][64 tokens]
-  uint8_t vt[D * kRow];  // V tile [d][64 tokens]
-  uint8_t ek[R * kRow];  // E_K^T tile [j][64 tokens]
-  uint8_t ev[R * kRow];  // E_V^T tile [j][64 tokens]
+  uint8_t x[D * kRow];     // K^T or V tile [d][64 tokens]
+  uint8_t e[2][R * kRow];  // E_K^T or E_V^T tiles [j][64 tokens]
 };
 
 template <int D, int R, bool kSmallP>
-__global__ __launch_bounds__(256) void compress_bf16_kernel(CompressParams p) {
+__global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_kernel(CompressParams p) {
   constexpr int DQ = D / 4, KG = 256 / DQ, KPT = kT / KG;  // key loads: 4 dims x KPT tokens
+  constexpr int NV = D / 32;           // 16-byte value loads per thread (8 rows per wave each)
+  constexpr int NE = R / 32;           // 16-byte projection loads per thread
+  // 32x32 output tiles, projection rows by d columns: waves in a WM x WN grid
+  // of NA x NB tiles each (rank 32 at d = 64 leaves two waves without one)
   constexpr int NMD = D / 32, NMR = R / 32;
-  constexpr int NTK = NMR * NMD;       // ck output tiles (cv has as many)
-  constexpr int TPW = 2 * NTK / 4;     // output tiles per wave
-  constexpr int NV = D / 32;           // 1-KB V loads per wave (8 rows x 128 B each)
-  constexpr int NE = R / 32;           // 1-KB loads per wave per projection
-  static_assert(KPT == 8 || KPT == 4, "layout");
+  constexpr int WM = NMR > 1 ? 2 : 1, WN = 4 / WM < NMD ? 4 / WM : NMD;
+  constexpr int NA = NMR / WM, NB = NMD / WN;
+  static_assert(KPT == 2 * NV, "key and value tiles take the same registers");
   __shared__ __attribute__((aligned(16))) CompressSmem<D, R> sm;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int h = blockIdx.y, b = blockIdx.z;
-  const int pi = blockIdx.x / p.parts, part = blockIdx.x % p.parts;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Workgroup ids go round-robin to the 8 XCDs; each XCD takes consecutive
+  // items of a batch entry (head, product, page, part), so that the few
+  // projections it reads stay in its L2.
+  const int per = p.n_pages * p.parts, G = per * 2 * p.H;
+  const int lin = (int)(blockIdx.y * gridDim.x + blockIdx.x), xcd = lin & 7;
+  const int item = xcd * (G >> 3) + min(xcd, G & 7) + (lin >> 3);
+  const int hk = item / per, pi = item % per / p.parts, part = item % p.parts;
+  const bool is_k = (hk & 1) == 0;
+  const int h = hk >> 1, b = blockIdx.z;
   const int page = p.first_page + pi;
   const int slot = clampi(p.page_table[(size_t)b * p.max_pages + page], 0, p.num_slots - 1);
   const size_t hb = (size_t)slot * p.H + h;
   const int P = p.P;
   const int t_beg = part * p.part_len, t_end = min(P, t_beg + p.part_len);
 
-  const uint16_t* kb = static_cast<const uint16_t*>(p.k) + hb * P * D;   // [P][D]
-  const uint16_t* vb = static_cast<const uint16_t*>(p.v) + hb * D * P;   // [D][P]
-  const uint16_t* ekb = static_cast<const uint16_t*>(p.e_k) + (size_t)h * R * P;  // [R][P]
-  const uint16_t* evb = static_cast<const uint16_t*>(p.e_v) + (size_t)h * R * P;
+  // ---- tile loads: one scalar base per tensor plus per-lane offsets, fixed
+  // for the whole page. Rows of 64 tokens (values, projections): instruction n
+  // of a wave covers 8 rows, source chunk (lane % 8) ^ swz(r) of row r lands at
+  // chunk lane % 8. Keys: 4 dims x KPT tokens per thread.
+  const uint16_t* xb = static_cast<const uint16_t*>(is_k ? p.k : p.v) + hb * P * D;      // [P][D] or [D][P]
+  const uint16_t* eb = static_cast<const uint16_t*>(is_k ? p.e_k : p.e_v) + (size_t)h * R * P;  // [R][P]
   const int dq = tid % DQ, kg = tid / DQ;
-
-  f32x16 acc[TPW];
+  auto row_of = [&](int n_inst, int n) { return (wave * n_inst + n) * 8 + (lane >> 3); };
+  auto col_of = [&](int r) { return 8 * ((lane & 7) ^ swz(r)); };
+  auto row_off = [&](int n_inst, int n) {
+    const int r = row_of(n_inst, n);
+    return (uint32_t)(r * P + (kSmallP ? min(col_of(r), P - 8) : col_of(r))) * 2u;
+  };
+  uint32_t v_off[NV], e_off[NE];
 #pragma unroll
-  for (int q = 0; q < TPW; ++q) acc[q] = f32x16{0};
-
-  for (int t0 = t_beg; t0 < t_end; t0 += kT) {
-    const int nv = min(kT, t_end - t0);
-    // window of the tile: 64 tokens ending at the page end when fewer remain
-    // (rows before the tile's first token are masked), or the whole page
-    // when it is shorter than a tile (rows past it are clamped and masked)
-    const int ws = kSmallP ? 0 : min(t0, P - kT);
-    const int lo = t0 - ws, hi = lo + nv;
-    // row-major tiles of 64 tokens: rows r = (wave * n_inst + n) * 8 + lane / 8,
-    // source chunk (lane % 8) ^ swz(r) lands at chunk lane % 8 of row r
-    auto row_load = [&](const uint16_t* base, int n_inst, uint8_t* dst, int n) {
-      const int r = (wave * n_inst + n) * 8 + (lane >> 3);
-      int col = 8 * ((lane & 7) ^ swz(r));
-      if constexpr (kSmallP) col = min(col, P - 8);
-      g2lds16(base + (size_t)r * P + ws + col, dst + (wave * n_inst + n) * 1024);
-    };
+  for (int n = 0; n < NV; ++n) v_off[n] = row_off(NV, n);
 #pragma unroll
-    for (int n = 0; n < NV; ++n) row_load(vb, NV, sm.vt, n);
+  for (int n = 0; n < NE; ++n) e_off[n] = row_off(NE, n);
+  const uint32_t k_off = (uint32_t)(kg * KPT * D + dq * 4) * 2u;
+  // A lane's operand of 16-token step ks in row block n (32 rows) of a tile
+  // sits at (o ^ 32 (ks ^ n)) + n blocks: swz of a row 32 n further differs by
+  // 2 n, and chunks are 16 bytes.
+  const int mt0 = (wave % WM) * NA, nt0 = (wave / WM) * NB;
+  const bool active = wave / WM < WN;
+  const uint32_t oa = (uint32_t)((mt0 * 32 + l32) * kRow + ((half ^ swz(mt0 * 32 + l32)) << 4));
+  const uint32_t ob = (uint32_t)((nt0 * 32 + l32) * kRow + ((half ^ swz(nt0 * 32 + l32)) << 4));
+  // The walk, for keys (kind true) or values: each compiled by itself, which
+  // takes fewer registers than one walk with both loads.
+  f32x16 acc[NA][NB];
 #pragma unroll
-    for (int n = 0; n < NE; ++n) row_load(ekb, NE, sm.ek, n);
+  for (int m = 0; m < NA; ++m)
 #pragma unroll
-    for (int n = 0; n < NE; ++n) row_load(evb, NE, sm.ev, n);
-    u32x2 kr[KPT];
+    for (int n = 0; n < NB; ++n) acc[m][n] = f32x16{0};
+  auto walk = [&](auto kind) {
+  constexpr bool K = decltype(kind)::value;
+  u32x4 x[2][NV];           // data of two tiles
+  // tile at t0: the 64-token window ending at the page end when fewer tokens
+  // remain, or the whole page when it is shorter than a tile (clamped)
+  auto window = [&](int t0) { return kSmallP ? 0 : min(t0, P - kT); };
+  auto load_x = [&](int t0, u32x4 (&xr)[NV]) {
+    if constexpr (K) {
+      const char* src = reinterpret_cast<const char*>(xb + (size_t)window(t0) * D);
+      u32x2 kr[KPT];
 #pragma unroll
-    for (int e = 0; e < KPT; ++e) {
-      int row = kg * KPT + e;
-      if constexpr (kSmallP) row = min(row, P - 1);
-      kr[e] = *reinterpret_cast<const u32x2*>(kb + (size_t)(ws + row) * D + dq * 4);
-    }
-    wait_vmcnt<0>();
-    // K^T: tokens outside [lo, hi) contribute zero
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int d = dq * 4 + c;
-      uint32_t w[KPT / 2];
-#pragma unroll
-      for (int e = 0; e < KPT / 2; ++e) {
-        const int r0 = kg * KPT + 2 * e;
-        const uint32_t x0 = c < 2 ? kr[2 * e].x : kr[2 * e].y;
-        const uint32_t x1 = c < 2 ? kr[2 * e + 1].x : kr[2 * e + 1].y;
-        const uint32_t h0 = (c & 1) ? (x0 >> 16) : (x0 & 0xffffu);
-        const uint32_t h1 = (c & 1) ? (x1 >> 16) : (x1 & 0xffffu);
-        const bool ok0 = r0 >= lo && r0 < hi, ok1 = r0 + 1 >= lo && r0 + 1 < hi;
-        w[e] = (ok0 ? h0 : 0u) | ((ok1 ? h1 : 0u) << 16);
+      for (int e = 0; e < KPT; ++e) {
+        uint32_t off = k_off + e * D * 2;
+        if constexpr (kSmallP) off -= (uint32_t)(max(0, kg * KPT + e - (P - 1)) * D * 2);
+        kr[e] = *reinterpret_cast<const u32x2*>(src + off);
       }
-      const int key0 = kg * KPT;
-      uint8_t* dst = &sm.kt[d * kRow + (((key0 >> 3) ^ swz(d)) << 4) + (key0 & 7) * 2];
-      if constexpr (KPT == 8) *reinterpret_cast<u32x4*>(dst) = u32x4{w[0], w[1], w[2], w[3]};
-      else *reinterpret_cast<u32x2*>(dst) = u32x2{w[0], w[1]};
-    }
-    __syncthreads();
-    if (lo > 0 || hi < kT) {
-      // E_V^T: the same tokens contribute zero to cv
-      for (int x = tid; x < R * kT; x += 256) {
-        const int j = x / kT, t = x % kT;
-        if (t < lo || t >= hi)
-          *reinterpret_cast<uint16_t*>(&sm.ev[j * kRow + (((t >> 3) ^ swz(j)) << 4) + (t & 7) * 2]) = 0;
-      }
-      __syncthreads();
-    }
 #pragma unroll
-    for (int ks = 0; ks < kT / 16; ++ks) {
-      const int chunk = 2 * ks + (lane >> 5);
+      for (int n = 0; n < NV; ++n) xr[n] = u32x4{kr[2 * n].x, kr[2 * n].y, kr[2 * n + 1].x, kr[2 * n + 1].y};
+    } else {
+      const char* src = reinterpret_cast<const char*>(xb + window(t0));
 #pragma unroll
-      for (int q = 0; q < TPW; ++q) {
-        const int ti = wave * TPW + q;
-        const uint8_t *ta, *tb;
-        int ra, rb;
-        if (ti < NTK) {  // ck[j][d] += E_K^T[j][t] K^T[d][t]
-          ra = (ti / NMD) * 32 + (lane & 31);
-          rb = (ti % NMD) * 32 + (lane & 31);
-          ta = sm.ek;
-          tb = sm.kt;
-        } else {         // cv[d][j] += V[d][t] E_V^T[j][t]
-          ra = ((ti - NTK) / NMR) * 32 + (lane & 31);
-          rb = ((ti - NTK) % NMR) * 32 + (lane & 31);
-          ta = sm.vt;
-          tb = sm.ev;
+      for (int n = 0; n < NV; ++n) xr[n] = ld_global16(src + v_off[n]);
+    }
+  };
+  // projections go straight into LDS, issued before the same step's data
+  // loads: waiting for them leaves those in flight
+  auto load_e = [&](int t0, int buf) {
+    const char* src = reinterpret_cast<const char*>(eb + window(t0));
+#pragma unroll
+    for (int n = 0; n < NE; ++n) g2lds16_hidden(src + e_off[n], sm.e[buf] + (wave * NE + n) * 1024);
+  };
+
+  // one tile: registers -> LDS, the loads of the tile after next, products
+  constexpr int kLoadsX = K ? KPT : NV;
+  auto step = [&](int t0, u32x4 (&xr)[NV], int buf) {
+    // valid tokens of this tile's window: [lo, hi), multiples of 8; the others
+    // are zeros in one operand (keys; the projection of the values)
+    const int lo = t0 - window(t0), hi = lo + min(kT, t_end - t0);
+    if constexpr (K) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int d = dq * 4 + c;
+        uint32_t w[KPT / 2];
+#pragma unroll
+        for (int e = 0; e < KPT / 2; ++e) {
+          const uint32_t x0 = c < 2 ? xr[e].x : xr[e].y, x1 = c < 2 ? xr[e].z : xr[e].w;
+          w[e] = (c & 1) ? __builtin_amdgcn_perm(x1, x0, 0x07060302) : __builtin_amdgcn_perm(x1, x0, 0x05040100);
         }
-        const u32x4 a = ld_lds16(ta + ra * kRow + ((chunk ^ swz(ra)) << 4));
-        const u32x4 bb = ld_lds16(tb + rb * kRow + ((chunk ^ swz(rb)) << 4));
-        acc[q] = mfma32(a, bb, acc[q]);
+        const int key0 = kg * KPT;  // KPT (4 or 8) tokens, on one side of lo and hi
+        if (key0 < lo || key0 >= hi)
+#pragma unroll
+          for (int e = 0; e < KPT / 2; ++e) w[e] = 0;
+        uint8_t* dst = &sm.x[d * kRow + (((key0 >> 3) ^ swz(d)) << 4) + (key0 & 7) * 2];
+        if constexpr (KPT == 8) *reinterpret_cast<u32x4*>(dst) = u32x4{w[0], w[1], w[2], w[3]};
+        else *reinterpret_cast<u32x2*>(dst) = u32x2{w[0], w[1]};
+      }
+    } else {
+#pragma unroll
+      for (int n = 0; n < NV; ++n) *reinterpret_cast<u32x4*>(sm.x + ((wave * NV + n) * 64 + lane) * 16) = xr[n];
+    }
+    // this tile's projection has landed: only the next tile's data is later
+    if (t0 + kT < t_end) wait_vmcnt<kLoadsX>();
+    else wait_vmcnt<0>();
+    if constexpr (!K) {
+      if (lo > 0 || hi < kT) {  // each lane clears what it loaded
+#pragma unroll
+        for (int n = 0; n < NE; ++n) {
+          const int col = col_of(row_of(NE, n));
+          if (col < lo || col >= hi)
+            *reinterpret_cast<u32x4*>(sm.e[buf] + ((wave * NE + n) * 64 + lane) * 16) = u32x4{0};
+        }
       }
     }
-    __syncthreads();
+    lds_barrier();
+    if (t0 + kT < t_end) load_e(t0 + kT, buf ^ 1);
+    if (t0 + 2 * kT < t_end) load_x(t0 + 2 * kT, xr);
+    if (active) {
+      // (opaque, so that the eight operand offsets are recomputed per tile
+      // instead of held across the walk)
+      uint32_t o_a = oa, o_b = ob;
+      asm volatile("" : "+v"(o_a), "+v"(o_b));
+#pragma unroll
+      for (int ks = 0; ks < kT / 16; ++ks) {
+        u32x4 a[NA];
+#pragma unroll
+        for (int m = 0; m < NA; ++m) a[m] = ld_lds16(sm.e[buf] + (o_a ^ ((ks ^ m) << 5)) + m * 32 * kRow);
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          const u32x4 bb = ld_lds16(sm.x + (o_b ^ ((ks ^ n) << 5)) + n * 32 * kRow);
+#pragma unroll
+          for (int m = 0; m < NA; ++m) acc[m][n] = mfma32(a[m], bb, acc[m][n]);
+        }
+      }
+    }
+    lds_barrier();
+  };
+  if (t_beg < t_end) {
+    load_e(t_beg, 0);
+    load_x(t_beg, x[0]);
+    if (t_beg + kT < t_end) load_x(t_beg + kT, x[1]);
   }
+  for (int t0 = t_beg; t0 < t_end; t0 += 2 * kT) {
+    step(t0, x[0], 0);
+    if (t0 + kT < t_end) step(t0 + kT, x[1], 1);
+  }
+  };
+  if (is_k) walk(std::true_type{});
+  else walk(std::false_type{});
 
-  // lane holds column (lane % 32) of each output tile, rows 8(r/4) + 4(lane/32) + r%4
+  // lane holds column d = 32 nt + lane % 32 of each tile, projection rows
+  // 32 mt + 8 (r / 4) + 4 (lane / 32) + r % 4
+  if (!active) return;
   uint16_t* ck = static_cast<uint16_t*>(p.ck) + hb * R * D;   // [R][D]
   uint16_t* cv = static_cast<uint16_t*>(p.cv) + hb * D * R;   // [D][R]
   float* part_out = p.parts > 1
       ? p.partial + ((((size_t)b * p.H + h) * p.n_pages + pi) * p.parts + part) * (2 * R * D)
       : nullptr;
 #pragma unroll
-  for (int q = 0; q < TPW; ++q) {
-    const int ti = wave * TPW + q;
-    const bool is_k = ti < NTK;
-    const int mt = is_k ? ti / NMD : (ti - NTK) / NMR;
-    const int nt = is_k ? ti % NMD : (ti - NTK) % NMR;
-    const int ncols = is_k ? D : R;
-    const int col = nt * 32 + (lane & 31);
+  for (int m = 0; m < NA; ++m)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = mt * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      const size_t e = (size_t)row * ncols + col;
-      if (part_out) {
-        part_out[(is_k ? 0 : R * D) + e] = acc[q][r];
-      } else {
-        const uint16_t v = (uint16_t)(pack_bf16(acc[q][r], 0.f) & 0xffffu);
-        if (is_k) ck[e] = v;
-        else cv[e] = v;
+    for (int n = 0; n < NB; ++n) {
+      const int d = 32 * (nt0 + n) + l32;
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const int j = 32 * (mt0 + m) + 8 * r4 + 4 * half;
+        const f32x4 v = f32x4{acc[m][n][4 * r4], acc[m][n][4 * r4 + 1], acc[m][n][4 * r4 + 2], acc[m][n][4 * r4 + 3]};
+        if (is_k) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if (part_out) part_out[(j + r) * D + d] = v[r];
+            else ck[(j + r) * D + d] = (uint16_t)(pack_bf16(v[r], 0.f) & 0xffffu);
+          }
+        } else if (part_out) {
+          *reinterpret_cast<f32x4*>(part_out + R * D + d * R + j) = v;
+        } else {
+          *reinterpret_cast<u32x2*>(cv + d * R + j) = u32x2{pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
+        }
       }
     }
-  }
 }
 
 // Sum of a page's parts in part order, rounded once to bf16. One workgroup
@@ -230,7 +297,7 @@ __global__ __launch_bounds__(256) void compress_f32_kernel(CompressParams p) {
 
 template <int D, int R>
 void launch_compress_bf16(const CompressParams& p, int B, hipStream_t s) {
-  const dim3 grid(p.n_pages * p.parts, p.H, B);
+  const dim3 grid(p.n_pages * p.parts, 2 * p.H, B);
   if (p.P < kT) compress_bf16_kernel<D, R, true><<<grid, 256, 0, s>>>(p);
   else compress_bf16_kernel<D, R, false><<<grid, 256, 0, s>>>(p);
 }

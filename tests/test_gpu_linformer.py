@@ -128,6 +128,27 @@ def test_fp32_tiny():
     _run(WORKLOADS["c1"], rank=32)
 
 
+@pytest.mark.parametrize("P,rank,d", [(8, 128, 128), (64, 32, 64), (72, 64, 128), (136, 128, 64),
+                                      (200, 64, 64), (328, 128, 128), (392, 32, 128)])
+def test_compress_whole_pages(P, rank, d):
+    # enough pages and heads that pages are not split into parts: walks of one
+    # to seven 64-token tiles per product, ragged last tiles, every rank and d
+    # (rank 32 at d = 64 leaves two waves of a workgroup without output tiles)
+    import torch
+    wl = SMALL.replace(page_size=P, head_dim=d, heads=8, k_h=(1,) * 8, n_cand=33, n_q=1, seed=74)
+    say(f"[case] compress whole pages P={P} rank={rank} d={d}")
+    case = make_case(wl)
+    dev = upload(case)
+    e_k, e_v = make_projections(wl, rank)
+    layer = _layer(wl, dev, e_k, e_v)
+    layer.ck.fill_(float("nan"))
+    layer.cv.fill_(float("nan"))
+    layer.compress(0, wl.n_pages)
+    torch.cuda.synchronize()
+    _check_compressed(layer, dict(k_pool=case.k_pool, v_pool=case.v_pool, page_table=case.page_table),
+                      e_k, e_v, wl, (0, 17, wl.n_pages - 1))
+
+
 def test_small_pages_and_meanpool():
     _run(SMALL.replace(page_size=8, n_cand=11, k_h=(1, 4, 6), seed=72), rank=32)
     _run(SMALL.replace(page_size=256, seed=73), rank=64, kind="meanpool")
