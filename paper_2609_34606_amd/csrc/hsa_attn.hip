@@ -92,9 +92,27 @@ __device__ __forceinline__ int key_perm(int m) {
   return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1);
 }
 
+__device__ __forceinline__ float sigmoid(float x) { return 1.f / (1.f + __expf(-x)); }
+
 // Gate weight sigmoid(g[i]); a missing gate array means logit 0 (weight 1/2).
 __device__ __forceinline__ float gate_w(const float* g, size_t i) {
-  return g ? 1.f / (1.f + __expf(-g[i])) : 0.5f;
+  return g ? sigmoid(g[i]) : 0.5f;
+}
+
+// The element-wise gate logits of a lane's 16 outputs in one 32-dim block:
+// four 16-byte loads per gate, issued together before the block's linear
+// branch is computed (16 dependent 4-byte loads per gate took a launch of 20
+// small items from 38 to 62 us). A missing array is logit 0.
+struct GateBlock {
+  f32x4 lin[4], sp[4];
+};
+__device__ __forceinline__ GateBlock load_gates(const AttnParams& p, size_t e0) {
+  GateBlock w;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) w.lin[g] = p.g_lin ? ld4u(p.g_lin + e0 + 8 * g) : f32x4{0};
+#pragma unroll
+  for (int g = 0; g < 4; ++g) w.sp[g] = p.g_sp ? ld4u(p.g_sp + e0 + 8 * g) : f32x4{0};
+  return w;
 }
 
 // Output of one (head, 128-query tile) from its normalised sparse-branch
@@ -142,7 +160,9 @@ __device__ __forceinline__ void finish(const AttnParams& p, uint8_t* smem, int b
       const float* lrow = p.o_lin + gi * D;
       uint16_t* orow = static_cast<uint16_t*>(p.o) + gi * D;
 #pragma unroll
-      for (int m = 0; m < NM; ++m)
+      for (int m = 0; m < NM; ++m) {
+        GateBlock gt;
+        if (p.gate_elem) gt = load_gates(p, gi * D + 32 * m + 4 * half);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int d0 = 32 * m + 8 * g + 4 * half;
@@ -151,14 +171,14 @@ __device__ __forceinline__ void finish(const AttnParams& p, uint8_t* smem, int b
           if (p.gate_elem) {
 #pragma unroll
             for (int q2 = 0; q2 < 4; ++q2)
-              v[q2] = gate_w(p.g_lin, gi * D + d0 + q2) * l[q2] +
-                      gate_w(p.g_sp, gi * D + d0 + q2) * inv_l * acc[m][4 * g + q2];
+              v[q2] = sigmoid(gt.lin[g][q2]) * l[q2] + sigmoid(gt.sp[g][q2]) * inv_l * acc[m][4 * g + q2];
           } else {
 #pragma unroll
             for (int q2 = 0; q2 < 4; ++q2) v[q2] = wl * l[q2] + a_sp * acc[m][4 * g + q2];
           }
           *reinterpret_cast<u32x2*>(orow + d0) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
         }
+      }
     }
     return;
   }
@@ -223,6 +243,8 @@ __device__ __forceinline__ void finish(const AttnParams& p, uint8_t* smem, int b
 #pragma unroll
     for (int mm = 0; mm < NM / 2; ++mm) {
       const int m = hf * (NM / 2) + mm;
+      GateBlock gt;
+      if (p.gate_elem && q_ok) gt = load_gates(p, gi * D + 32 * m + 4 * half);
       f32x16 al = f32x16{0};
       const int row = 32 * mm + l32;  // row within the staged half
 #pragma unroll
@@ -239,8 +261,8 @@ __device__ __forceinline__ void finish(const AttnParams& p, uint8_t* smem, int b
           if (p.gate_elem) {
 #pragma unroll
             for (int q2 = 0; q2 < 4; ++q2)
-              v[q2] = gate_w(p.g_lin, gi * D + d0 + q2) * inv_den * al[4 * g + q2] +
-                      gate_w(p.g_sp, gi * D + d0 + q2) * inv_l * acc[m][4 * g + q2];
+              v[q2] = sigmoid(gt.lin[g][q2]) * inv_den * al[4 * g + q2] +
+                      sigmoid(gt.sp[g][q2]) * inv_l * acc[m][4 * g + q2];
           } else {
 #pragma unroll
             for (int q2 = 0; q2 < 4; ++q2) v[q2] = a_lin * al[4 * g + q2] + a_sp * acc[m][4 * g + q2];
@@ -1176,23 +1198,29 @@ namespace {
 // Stream-K ranges of the page walk. The launch's items (b, h, 256-query
 // tile; a head's items all cost its list's tiles) are laid end to end, tile
 // by tile, and cut into G equal ranges of consecutive tiles, one workgroup
-// each: G = 256 (one per CU) unless the launch has fewer than 16 tiles per
+// each: G = 256 (one per CU) unless the launch has fewer than 8 tiles per
 // range or two ranges per item (the partial slots: each range holds at most
 // two pieces of cut items, its first and last segments). Items of equal
 // length that fill at least 7/8 of the CUs whole (one or more per range)
 // are not cut: the partial outputs, merges and second prologues of cut
 // items cost more there than the idle CUs. Launches of at least 4 x 256
 // items, and launches of at most 256 items whose longest item is at most
-// kCutTiles longer than a range, take one whole item per workgroup
+// kCutTiles longer than a range (four tiles at two ranges per item, where
+// most ranges are one piece; else ten, since most ranges then hold two), take
+// one whole item per workgroup
 // (sk_whole): with many items per
 // range, the 32 ranges running on an XCD would each walk a different head
 // and share no page in its L2 (30 batched layers of the streaming workload:
 // 17.4 against 14.7 ms per chunk), while the dispatcher's own balancing
-// leaves a tail of at most one item in four. split = false (fp32, whose
-// kernel does not read the schedule) takes one range.
+// leaves a tail of at most one item in four. Small launches are bound by the
+// length of a range's serial walk (d = 64: 1.15 us per tile and 9 us around
+// it): 20 items of 12 to 28 tiles took 38 us in 23 ranges of at least 16 tiles
+// and take 31 us in 40 (4, 6 and 8 as the least tiles alike, the two ranges
+// per item bind). split = false (fp32, whose kernel does not read the
+// schedule) takes one range.
 bool plan_stream_k(AttnParams& p, int B, int H, int n_q, int P, const int* list_len, int max_part,
                    bool split) {
-  constexpr int kMaxRanges = 256, kMinTiles = 16, kWholeItems = 4 * kMaxRanges, kCutTiles = 4;
+  constexpr int kMaxRanges = 256, kMinTiles = 8, kWholeItems = 4 * kMaxRanges;
   const int nqt = (n_q + 255) / 256, tpp = (P + kBN - 1) / kBN;
   int64_t per_b = 0;
   for (int h = 0; h < H; ++h) {
@@ -1211,7 +1239,9 @@ bool plan_stream_k(AttnParams& p, int B, int H, int n_q, int P, const int* list_
   // whole items also when the launch holds at most one item per CU and its
   // longest item is at most a few tiles longer than a range: cutting then
   // saves less than the second prologue and the merge of a cut item cost
-  // (the Linformer branch over compressed pages: items of 5-19 tiles)
+  // (the Linformer branch over compressed pages, items of 5-19 tiles: 48 us
+  // whole, 74 us cut into ranges)
+  const int kCutTiles = G >= 2 * items ? 4 : 10;
   int max_len = 1;
   for (int h = 0; h < H; ++h) max_len = std::max(max_len, std::max(1, list_len[h]) * tpp);
   const bool whole = split && items <= INT32_MAX &&

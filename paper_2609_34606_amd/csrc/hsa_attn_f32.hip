@@ -39,16 +39,6 @@ constexpr int kQB = 64;    // queries per workgroup
 constexpr int kTK = 32;    // keys per tile of one stream
 constexpr int kWaves = 8;  // 4 query groups x 2 key streams
 
-// four floats at 4-byte alignment (one global access)
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
-__device__ __forceinline__ f32x4 ld4u(const float* p) {
-  const f32x4u v = *reinterpret_cast<const f32x4u*>(p);
-  return f32x4{v.x, v.y, v.z, v.w};
-}
-__device__ __forceinline__ void st4u(float* p, f32x4 v) {
-  *reinterpret_cast<f32x4u*>(p) = f32x4u{v.x, v.y, v.z, v.w};
-}
 __device__ __forceinline__ f32x4 ld4s(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
 // D[16x16] += A[16x4] B[4x16]: lane l supplies A row l % 16 and B column
@@ -463,7 +453,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
     continue;
   }
   // gate weights: one per (query, head), or per element with gate_elem
-  auto sig = [](const float* gt, size_t i) { return gt ? 1.f / (1.f + expf(-gt[i])) : 0.5f; };
+  auto sigm = [](float x) { return 1.f / (1.f + expf(-x)); };
+  auto sig = [&](const float* gt, size_t i) { return gt ? sigm(gt[i]) : 0.5f; };
   float wl = 0.5f, wsp = 0.5f;
   if (q_ok && !p.gate_elem) {
     wl = sig(p.g_lin, gi);
@@ -472,10 +463,12 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
   auto write = [&](int i, f32x4 lin) {  // lin: the linear branch's four values
     if (!q_ok) return;
     const size_t e0 = gi * D + 16 * (s * NH + i) + 4 * g;
-    f32x4 o;
+    f32x4 gl = f32x4{0}, gs = f32x4{0}, o;
+    if (p.gate_elem && p.g_lin) gl = ld4u(p.g_lin + e0);
+    if (p.gate_elem && p.g_sp) gs = ld4u(p.g_sp + e0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float a = p.gate_elem ? sig(p.g_lin, e0 + r) : wl, c = p.gate_elem ? sig(p.g_sp, e0 + r) : wsp;
+      const float a = p.gate_elem ? sigm(gl[r]) : wl, c = p.gate_elem ? sigm(gs[r]) : wsp;
       o[r] = a * lin[r] + c * oa[i][r] * inv_l;
     }
     st4u(static_cast<float*>(p.o) + e0, o);

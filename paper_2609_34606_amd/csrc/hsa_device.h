@@ -46,6 +46,15 @@ __device__ __forceinline__ float phi(float x) { return x > 0.f ? x + 1.f : __exp
 __device__ __forceinline__ u32x4 ld_global16(const void* p) {
   return *reinterpret_cast<const u32x4*>(p);
 }
+// Four floats at 4-byte alignment (one global access).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 ld4u(const float* p) {
+  const f32x4u v = *reinterpret_cast<const f32x4u*>(p);
+  return f32x4{v.x, v.y, v.z, v.w};
+}
+__device__ __forceinline__ void st4u(float* p, f32x4 v) {
+  *reinterpret_cast<f32x4u*>(p) = f32x4u{v.x, v.y, v.z, v.w};
+}
 __device__ __forceinline__ u32x4 ld_lds16(const void* p) {
   return *reinterpret_cast<const u32x4*>(p);
 }

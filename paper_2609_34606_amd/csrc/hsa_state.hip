@@ -292,8 +292,6 @@ __global__ __launch_bounds__(256, 2) void state_bf16_kernel(StateParams p) {
 // Measured: 19 pages of 392 keys x 8 heads x d128 36 us (1.95 GFLOP, 61 MB and
 // 60 MB of partial states written and read; VALU kernel before it 168 us), 9
 // pages of 256 x 2 heads x d64 6 us (18 us).
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
 template <int D>
 struct StateF32Smem {
   static constexpr int kKeys = 32;
@@ -341,15 +339,11 @@ __global__ __launch_bounds__(256, 2) void state_f32_kernel(StateParams p) {
     const float* kp = kb + hb * p.P * D + 4 * kc;
     const float* vp = vb + hb * D * p.P;
 #pragma unroll
-    for (int n = 0; n < NLD; ++n) {
-      const f32x4u x = *reinterpret_cast<const f32x4u*>(kp + (size_t)min(k0 + kr0 + RG * n, k_end - 1) * D);
-      kr[n] = f32x4{x.x, x.y, x.z, x.w};
-    }
+    for (int n = 0; n < NLD; ++n) kr[n] = ld4u(kp + (size_t)min(k0 + kr0 + RG * n, k_end - 1) * D);
 #pragma unroll
     for (int n = 0; n < NLD; ++n) {
       const int x = tid + 256 * n;
-      const f32x4u y = *reinterpret_cast<const f32x4u*>(vp + (size_t)(x >> 3) * p.P + min(k0 + 4 * (x & 7), k_end - 4));
-      vr[n] = f32x4{y.x, y.y, y.z, y.w};
+      vr[n] = ld4u(vp + (size_t)(x >> 3) * p.P + min(k0 + 4 * (x & 7), k_end - 4));
     }
     nk = min(T, k_end - k0);
     unit = u;
