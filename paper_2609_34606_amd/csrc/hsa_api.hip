@@ -204,19 +204,24 @@ Scratch f32_scratch(void* ws, size_t ws_bytes, size_t need) {
   return Scratch{static_cast<uint8_t*>(ws) + need, ws_bytes - need};
 }
 
-// The attention launch of a planned call: bf16 with its split partials set,
+// The scratch of a planned attention launch: bf16 with its split partials set,
 // fp32 planned here for the scratch it was given.
-hsa_status_t run_attention(const hsa_config_t* c, int n_q, const int* list_len, AttnParams& p,
-                           void* partials, const Scratch& f32, hipStream_t s) {
-  hipError_t e;
+void set_scratch(const hsa_config_t* c, int n_q, const int* list_len, AttnParams& p, void* partials,
+                 const Scratch& f32) {
   if (c->dtype == HSA_DTYPE_BF16) {
     set_partials(p, c, n_q, partials);
-    e = launch_attention_bf16(c->head_dim, c->batch, p, s);
+    p.n_ctr = p.sc.n_chead > 0 ? c->batch * c->num_heads * p.sc.nqt : 0;
   } else {
     plan_attention_f32(p, c->batch, c->num_heads, c->head_dim, n_q, p.P, list_len, f32.bytes);
     set_partials_f32(p, c->head_dim, f32.base);
-    e = launch_attention_f32(c->head_dim, c->batch, p, s);
   }
+}
+
+// cleared: an earlier launch of this call has cleared the arrival counters.
+hsa_status_t launch_attention(const hsa_config_t* c, const AttnParams& p, bool cleared, hipStream_t s) {
+  if (!cleared) zero_counters(p, s);
+  const hipError_t e = c->dtype == HSA_DTYPE_BF16 ? launch_attention_bf16(c->head_dim, c->batch, p, s)
+                                                  : launch_attention_f32(c->head_dim, p, s);
   return e == hipSuccess ? HSA_OK : HSA_ERR_DEVICE;
 }
 
@@ -399,10 +404,23 @@ size_t o_lin_bytes(const hsa_config_t* c, int n_q) {
   return align_up((size_t)c->batch * n_q * c->num_heads * c->head_dim * 4);
 }
 
+// Stage 1 of a retrieval call, scored in the page selection's first launch.
+struct Stage1 {
+  const float* prompt;
+  const float* chunks;
+  const int32_t* chunk_first;
+  int E, M;
+  int32_t* chunk_out;
+  double* cos;  // scratch [B, M]
+};
+
+// Page selection; attn: the planned attention launch that follows (its arrival
+// counters are cleared here). The candidates are the pages [0, n_cand), those
+// of cand_range, or those of Stage 1's chunk.
 hsa_status_t run_select(const hsa_config_t* c, const void* q, int n_q, const double* kmean,
                         int max_pages, int n_cand, const int32_t* k_h, int k_max, int32_t* sel,
-                        double* sel_score, void* ws, hipStream_t s,
-                        const int32_t* cand_range = nullptr) {
+                        double* sel_score, void* ws, hipStream_t s, const AttnParams* attn = nullptr,
+                        const int32_t* cand_range = nullptr, const Stage1* st1 = nullptr) {
   QsumParams qp{};
   qp.q = q;
   qp.n_q = n_q;
@@ -423,6 +441,20 @@ hsa_status_t run_select(const hsa_config_t* c, const void* q, int n_q, const dou
   sp.sel = sel;
   sp.sel_score = sel_score;
   sp.cand_range = cand_range;
+  if (st1) {
+    qp.prompt = st1->prompt;
+    qp.chunks = st1->chunks;
+    qp.E = st1->E;
+    sp.M = qp.M = st1->M;
+    qp.chunk_cos = st1->cos;
+    sp.chunk_cos = st1->cos;
+    sp.chunk_first = st1->chunk_first;
+    sp.chunk_out = st1->chunk_out;
+  }
+  if (attn) {
+    sp.zero = attn->attn_ctr;
+    sp.n_zero = attn->n_ctr;
+  }
   return from_hip(launch_page_select(c->dtype, c->head_dim, c->batch, qp, sp, s));
 }
 
@@ -474,8 +506,9 @@ hsa_status_t run_sparse(const hsa_config_t* cfg, const void* q, int32_t n_q,
   if (!plan_attention(p, cfg->batch, cfg->num_heads, cfg->head_dim, n_q, cfg->page_size, list_len,
                       kPartPerHead * cfg->num_heads, cfg->dtype == HSA_DTYPE_BF16, w ? 4 : kPageWaves))
     return HSA_ERR_UNSUPPORTED;
+  set_scratch(cfg, n_q, list_len, p, partials, f32);
   if (w) set_block_lists(p, *w, static_cast<uint8_t*>(partials) - w->part_off);
-  return run_attention(cfg, n_q, list_len, p, partials, f32, s);
+  return launch_attention(cfg, p, false, s);
 }
 
 }  // namespace
@@ -760,15 +793,15 @@ bool plan_attend(AttnParams& p, const hsa_config_t* cfg, int n_q, const int32_t*
                         tile_lists ? 4 : kPageWaves);
 }
 
-// Sparse branch + linear branch + gated fusion for a selection in `sel`.
-hsa_status_t run_attend(const hsa_config_t* cfg, const void* q, int32_t n_q,
-                        const hsa_kv_pool_t* pool, const int32_t* sel, int32_t k_max,
-                        const int32_t* k_h, int32_t n_cand, int32_t n_cur_pages,
-                        const float* kv_state, const float* k_state, const float* g_lin,
-                        const float* g_sp, void* o, void* partials, const Scratch& f32, hipStream_t s,
-                        const AdaptiveWs* w = nullptr, uint8_t* wbase = nullptr,
-                        const float* o_lin = nullptr) {
-  AttnParams p{};
+// Sparse branch + linear branch + gated fusion for a selection in `sel`:
+// everything but the launch.
+hsa_status_t prepare_attend(AttnParams& p, const hsa_config_t* cfg, const void* q, int32_t n_q,
+                            const hsa_kv_pool_t* pool, const int32_t* sel, int32_t k_max,
+                            const int32_t* k_h, int32_t n_cand, int32_t n_cur_pages,
+                            const float* kv_state, const float* k_state, const float* g_lin,
+                            const float* g_sp, void* o, void* partials, const Scratch& f32,
+                            const AdaptiveWs* w = nullptr, uint8_t* wbase = nullptr,
+                            const float* o_lin = nullptr) {
   p.o_lin = o_lin;
   p.q = q;
   p.k = pool->k;
@@ -794,8 +827,9 @@ hsa_status_t run_attend(const hsa_config_t* cfg, const void* q, int32_t n_q,
   p.o = o;
   int list_len[HSA_MAX_HEADS];
   if (!plan_attend(p, cfg, n_q, k_h, n_cand, n_cur_pages, w != nullptr, list_len)) return HSA_ERR_UNSUPPORTED;
+  set_scratch(cfg, n_q, list_len, p, partials, f32);
   if (w) set_block_lists(p, *w, wbase);
-  return run_attention(cfg, n_q, list_len, p, partials, f32, s);
+  return HSA_OK;
 }
 
 // hsa_forward after its checks: page selection into sel_out (or the
@@ -809,11 +843,13 @@ hsa_status_t forward_body(const hsa_config_t* cfg, const void* q, int32_t n_q,
                           const Scratch& f32, hipStream_t s) {
   int32_t* sel = sel_out ? sel_out : reinterpret_cast<int32_t*>(base + select_ws_bytes(cfg, n_q));
   void* partials = base + select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max);
-  hsa_status_t st =
-      run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, base, s);
+  AttnParams p{};
+  hsa_status_t st = prepare_attend(p, cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state,
+                                   k_state, g_lin, g_sp, o, partials, f32);
   if (st != HSA_OK) return st;
-  return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, partials, f32, s);
+  st = run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, base, s, &p);
+  if (st != HSA_OK) return st;
+  return launch_attention(cfg, p, true, s);
 }
 
 }  // namespace
@@ -856,8 +892,11 @@ hsa_status_t hsa_forward_selected(const hsa_config_t* cfg, const void* q, int32_
   if ((st = validate_selection(cfg, pool, sel, k_max, s)) != HSA_OK) return st;
   uint8_t* base = static_cast<uint8_t*>(ws);
   void* partials = base + select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max);
-  return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, partials, f32_scratch(ws, ws_bytes, need), s);
+  AttnParams p{};
+  st = prepare_attend(p, cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
+                      g_lin, g_sp, o, partials, f32_scratch(ws, ws_bytes, need));
+  if (st != HSA_OK) return st;
+  return launch_attention(cfg, p, false, s);
 }
 
 hsa_status_t hsa_forward_adaptive(const hsa_config_t* cfg, const void* q, int32_t n_q,
@@ -878,13 +917,16 @@ hsa_status_t hsa_forward_adaptive(const hsa_config_t* cfg, const void* q, int32_
   if ((st = validate_pages(cfg, pool, 0, n_cand + n_cur_pages, s)) != HSA_OK) return st;
   uint8_t* base = static_cast<uint8_t*>(ws);
   int32_t* sel = sel_out ? sel_out : reinterpret_cast<int32_t*>(base + w.sel_off);
-  st = run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, ws, s);
+  AttnParams p{};
+  st = prepare_attend(p, cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state, g_lin,
+                      g_sp, o, base + w.part_off, f32_scratch(ws, ws_bytes, w.total), &w, base);
+  if (st != HSA_OK) return st;
+  st = run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, ws, s, &p);
   if (st != HSA_OK) return st;
   st = run_block_select(cfg, q, n_q, pool, sel, k_max, n_cand, n_cur_pages, tau_min, tau_max, w,
                         base, true, BlockSelOut(), s);
   if (st != HSA_OK) return st;
-  return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, base + w.part_off, f32_scratch(ws, ws_bytes, w.total), s, &w, base);
+  return launch_attention(cfg, p, true, s);
 }
 
 hsa_status_t hsa_chunk_select(const hsa_config_t* cfg, const float* prompt_emb,
@@ -935,16 +977,32 @@ hsa_status_t hsa_forward_retrieval(const hsa_config_t* cfg, const void* q, int32
   if ((st = validate_pages(cfg, pool, 0, n_cand + n_cur_pages, s)) != HSA_OK) return st;
   uint8_t* base = static_cast<uint8_t*>(ws);
   int32_t* range = reinterpret_cast<int32_t*>(base + fwd);
-  st = hsa_chunk_select(cfg, prompt_emb, chunk_emb, emb_dim, n_chunks, chunk_first, n_cand,
-                        chunk_out, nullptr, range, stream);
-  if (st != HSA_OK) return st;
   int32_t* sel = sel_out ? sel_out : reinterpret_cast<int32_t*>(base + select_ws_bytes(cfg, n_q));
-  void* partials = base + select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max);
-  st = run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, ws, s,
-                  range);
+  uint8_t* partials = base + select_ws_bytes(cfg, n_q) + sel_ws_bytes(cfg, k_max);
+  const Scratch f32 = f32_scratch(ws, ws_bytes, need);
+  AttnParams p{};
+  st = prepare_attend(p, cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
+                      g_lin, g_sp, o, partials, f32);
   if (st != HSA_OK) return st;
-  return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, kv_state, k_state,
-                    g_lin, g_sp, o, partials, f32_scratch(ws, ws_bytes, need), s);
+  // Stage 1's scores go where the attention's partials will be, before its
+  // arrival counters; with no room there, Stage 1 is a launch of its own
+  uint8_t* room = cfg->dtype == HSA_DTYPE_BF16 ? partials : static_cast<uint8_t*>(f32.base);
+  size_t room_bytes = cfg->dtype == HSA_DTYPE_BF16 ? partial_ws_bytes(cfg, n_q) : f32.bytes;
+  if (p.n_ctr > 0) room_bytes = reinterpret_cast<uint8_t*>(p.attn_ctr) - room;
+  if (room && (size_t)cfg->batch * n_chunks * 8 <= room_bytes) {
+    const Stage1 st1{prompt_emb, chunk_emb, chunk_first, emb_dim, n_chunks, chunk_out,
+                     reinterpret_cast<double*>(room)};
+    st = run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, ws, s, &p,
+                    nullptr, &st1);
+  } else {
+    st = hsa_chunk_select(cfg, prompt_emb, chunk_emb, emb_dim, n_chunks, chunk_first, n_cand, chunk_out,
+                          nullptr, range, stream);
+    if (st != HSA_OK) return st;
+    st = run_select(cfg, q, n_q, page_kmean, pool->max_pages, n_cand, k_h, k_max, sel, nullptr, ws, s, &p,
+                    range);
+  }
+  if (st != HSA_OK) return st;
+  return launch_attention(cfg, p, true, s);
 }
 
 size_t hsa_linformer_compress_workspace_size(const hsa_config_t* cfg, int32_t rank,
@@ -1032,8 +1090,12 @@ hsa_status_t hsa_forward_linformer(const hsa_config_t* cfg, const void* q, int32
   st = run_sparse(&cr, q, n_q, &cpool, sel, k_max, k_h, n_cand, n_cur_pages, o_lin, nullptr,
                   base + w.part_off, f32, nullptr, s);
   if (st != HSA_OK) return st;
-  return run_attend(cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, nullptr, nullptr,
-                    g_lin, g_sp, o, base + w.part_off, f32, s, &w, base, o_lin);
+  // (the branch above leaves its partials where this launch's counters are)
+  AttnParams p{};
+  st = prepare_attend(p, cfg, q, n_q, pool, sel, k_max, k_h, n_cand, n_cur_pages, nullptr, nullptr,
+                      g_lin, g_sp, o, base + w.part_off, f32, &w, base, o_lin);
+  if (st != HSA_OK) return st;
+  return launch_attention(cfg, p, false, s);
 }
 
 }  // extern "C"

@@ -1452,14 +1452,13 @@ bool plan_schedule(AttnParams& p, int H, int d, int n_q, int P, const int* list_
 
 }  // namespace
 
-// arrival counters of the split tiles (a fill kernel, not a memset, so that
-// the launch sequence can be captured into a graph)
-void zero_counters(int32_t* ctr, int n, hipStream_t s) {
-  zero_counters_kernel<<<(n + 255) / 256, 256, 0, s>>>(ctr, n);
+// (a fill kernel, not a memset, so that the launch sequence can be captured
+// into a graph)
+void zero_counters(const AttnParams& p, hipStream_t s) {
+  if (p.n_ctr > 0) zero_counters_kernel<<<(p.n_ctr + 255) / 256, 256, 0, s>>>(p.attn_ctr, p.n_ctr);
 }
 
 hipError_t launch_attention_bf16(int d, int B, const AttnParams& p, hipStream_t s) {
-  if (p.sc.n_chead > 0) zero_counters(p.attn_ctr, B * p.H * p.sc.nqt, s);
   const bool small = p.P < kBN, list = p.blist != nullptr;
   // tile lists (block-sparse mode) are built per 128-query tile and walked
   // by 4-wave workgroups; the page walk takes 8-wave ones, one per range

@@ -578,6 +578,7 @@ size_t plan_attention_f32(AttnParams& p, int B, int H, int d, int n_q, int P, co
   p.sc.sk_q = (int32_t)(T / G);
   p.sc.sk_rm = (int32_t)(T % G);
   p.sc.n_chead = whole ? 0 : 1;
+  p.n_ctr = whole ? 0 : (int32_t)items;
   return whole ? 0 : partial_bytes(d, items, G);
 }
 
@@ -586,8 +587,7 @@ void set_partials_f32(AttnParams& p, int d, void* base) {
   p.attn_ctr = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(base) + (size_t)p.sc.sk_g * 2 * slot_bytes(d));
 }
 
-hipError_t launch_attention_f32(int d, int B, const AttnParams& p, hipStream_t s) {
-  if (p.sc.n_chead > 0) zero_counters(p.attn_ctr, (int)items_of(B, p.H, p.n_q), s);
+hipError_t launch_attention_f32(int d, const AttnParams& p, hipStream_t s) {
   const dim3 grid(p.sc.sk_g), block(64 * kWaves);
   if (p.blist) {
     if (d == 128) attn_f32_kernel<128, true><<<grid, block, 0, s>>>(p);

@@ -47,6 +47,11 @@ struct QsumParams {
   int32_t n_q, HD;          // HD = H * d
   int32_t rows_per_split, n_split;
   double* ws_qs;            // [B, n_split, H*d]
+  // Stage-1 scores in the same launch (chunk_cos != NULL)
+  const float* prompt;      // [B, E]
+  const float* chunks;      // [B, M, E]
+  int32_t E, M;
+  double* chunk_cos;        // [B, M]
 };
 
 struct SelectParams {
@@ -58,6 +63,15 @@ struct SelectParams {
   double* sel_score;        // nullable
   const int32_t* cand_range;  // [B, 2] candidate pages [lo, hi) of each batch
                               // entry (Stage-1 chunk), nullable: [0, n_cand)
+  // Stage-1 scores of the first launch (NULL: none): the candidates are the
+  // pages of the best chunk
+  const double* chunk_cos;    // [B, M]
+  const int32_t* chunk_first; // [B, M + 1]
+  int32_t M;
+  int32_t* chunk_out;         // [B] nullable
+  // arrival counters of the attention launch that follows, cleared on the way
+  int32_t* zero;
+  int32_t n_zero;
 };
 
 // Stage-1 prompt-level retrieval: top-1 chunk by cosine similarity.
@@ -228,7 +242,10 @@ struct AttnParams {
   float* part_o;                         // [B, n_part, nq32, d/32 x 16 registers, 64 lanes]
   float* part_lse;                       // [B, n_part, nq32, 64 lanes]
   int32_t* attn_ctr;                     // [B, H, nqt] arrivals of the splits of each query
-                                         // tile (zeroed by the launch)
+                                         // tile: n_ctr of them (0: no item is cut), cleared
+                                         // before the launch (zero_counters, or the
+                                         // page selection)
+  int32_t n_ctr;
   // block-sparse mode (blist != NULL): each (b, h, query tile) walks its own
   // list of 64-key tiles, entry {slot * H + h, (tile index << 2) | mask}; mask
   // bit w covers query block 2 * qtile + w (waves 2w, 2w + 1)
@@ -260,8 +277,8 @@ size_t attention_partial_o_bytes(int B, int d, int n_q, int n_part);
 size_t attention_partial_lse_bytes(int B, int n_q, int n_part);
 
 hipError_t launch_attention_bf16(int d, int B, const AttnParams& p, hipStream_t s);
-// Zeroes n arrival counters.
-void zero_counters(int32_t* ctr, int n, hipStream_t s);
+// Clears a planned launch's arrival counters, if it has any.
+void zero_counters(const AttnParams& p, hipStream_t s);
 
 // fp32 attention. plan_attention_f32 fills p.sc: the steps (64 keys of one 64-query
 // item) of each head's items (sk_head_off, within a batch entry), the equal
@@ -274,6 +291,6 @@ size_t attention_f32_partial_bytes(int B, int H, int d, int n_q);
 size_t plan_attention_f32(AttnParams& p, int B, int H, int d, int n_q, int P, const int* list_len,
                           size_t avail);
 void set_partials_f32(AttnParams& p, int d, void* base);
-hipError_t launch_attention_f32(int d, int B, const AttnParams& p, hipStream_t s);
+hipError_t launch_attention_f32(int d, const AttnParams& p, hipStream_t s);
 
 }  // namespace hsa

@@ -34,12 +34,95 @@ __device__ __forceinline__ void load8<float>(const float* p, float (&x)[8]) {
   x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
+// Per-lane partial sums of a.b and a.a over E elements: a lane reads VW
+// consecutive floats per access (VW = 4: 16-byte loads) and issues U accesses
+// of each array per round before using them (the pass is latency-bound); the products
+// of a round go to eight fp64 partials in a fixed order.
+template <int VW, int U>
+__device__ __forceinline__ void dot_norm(const float* a, const float* bv, int E, int lane,
+                                         double (&dot)[8], double (&na)[8]) {
+  const int n = E / VW;
+  for (int g0 = lane; g0 < n; g0 += 64 * U) {
+    typedef float V __attribute__((ext_vector_type(VW)));
+    V x[U], y[U];
+    // unconditional (clamped) loads, all issued before the first is used
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int g = min(g0 + 64 * u, n - 1);
+      x[u] = reinterpret_cast<const V*>(a)[g];
+      y[u] = reinterpret_cast<const V*>(bv)[g];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g0 + 64 * u >= n) x[u] = y[u] = V{0};
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < VW; ++e) {
+        const int k = (u * VW + e) & 7;
+        dot[k] = fma((double)x[u][e], (double)y[u][e], dot[k]);
+        na[k] = fma((double)x[u][e], (double)x[u][e], na[k]);
+      }
+  }
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
+  return v;
+}
+
+// One wave's dot product a.b and squared norm a.a over E elements: eight fp64
+// partials per lane, added in a fixed pairwise order, then a fixed butterfly.
+// 16-byte loads when every row starts 16-byte aligned (vec).
+// U16: 16-byte loads in flight per array (the sums do not depend on it).
+template <int U16>
+__device__ __forceinline__ void dot_and_norm(const float* a, const float* bv, int E, int lane, bool vec,
+                                             double& dot, double& norm) {
+  auto lane_sum = [](const double (&x)[8]) {
+    return ((x[0] + x[4]) + (x[2] + x[6])) + ((x[1] + x[5]) + (x[3] + x[7]));
+  };
+  double d8[8], n8[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) d8[k] = n8[k] = 0.0;
+  if (vec) dot_norm<4, U16>(a, bv, E, lane, d8, n8);
+  else dot_norm<1, 8>(a, bv, E, lane, d8, n8);
+  dot = wave_sum(lane_sum(d8));
+  norm = wave_sum(lane_sum(n8));
+}
+
+__device__ __forceinline__ bool rows_aligned(int E, const float* a, const float* b) {
+  return (E & 3) == 0 && ((uintptr_t)a & 15) == 0 && ((uintptr_t)b & 15) == 0;
+}
+
+// (p . c) / (|p| |c|), 0 when a norm is 0
+__device__ __forceinline__ double cosine(double dot, double cc, double pp) {
+  const double den = sqrt(cc) * sqrt(pp);
+  return den > 0.0 ? dot / den : 0.0;
+}
+
 // Column sums of a block of query rows, fp64: ws_qs[b][split][c]. Rows are
 // read sixteen at a time so that the loads are in flight together; the sum
-// still runs over the rows in increasing order.
-template <typename T>
+// still runs over the rows in increasing order. Workgroups past the splits
+// score one chunk each for a retrieval call (the prompt's norm on a wave of
+// its own): the scores take no longer than the sums beside them, where a
+// launch of one workgroup per batch entry took 31 us (24 chunks of 4096).
+template <typename T, bool kStage1>
 __global__ __launch_bounds__(256) void qsum_kernel(QsumParams p) {
   const int b = blockIdx.y, split = blockIdx.x;
+  if (kStage1 && split >= p.n_split) {
+    __shared__ double pp;
+    const int m = split - p.n_split, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float* pr = p.prompt + (size_t)b * p.E;
+    const float* ch = p.chunks + ((size_t)b * p.M + m) * p.E;
+    double dot = 0.0, norm = 0.0;
+    if (wave < 2) dot_and_norm<8>(wave == 0 ? ch : pr, pr, p.E, lane, rows_aligned(p.E, p.prompt, p.chunks), dot, norm);
+    if (wave == 1 && lane == 0) pp = norm;
+    __syncthreads();
+    if (wave == 0 && lane == 0) p.chunk_cos[(size_t)b * p.M + m] = cosine(dot, norm, pp);
+    return;
+  }
   const int r0 = split * p.rows_per_split;
   const int r1 = min(p.n_q, r0 + p.rows_per_split);
   const T* q = static_cast<const T*>(p.q) + (size_t)b * p.n_q * p.HD;
@@ -51,6 +134,7 @@ __global__ __launch_bounds__(256) void qsum_kernel(QsumParams p) {
       float x[16][8];
 #pragma unroll
       for (int u = 0; u < 16; ++u) load8<T>(q + (size_t)(r + u) * p.HD + vc * 8, x[u]);
+      __builtin_amdgcn_sched_barrier(0);  // no use between the loads
 #pragma unroll
       for (int u = 0; u < 16; ++u)
 #pragma unroll
@@ -85,6 +169,27 @@ __device__ __forceinline__ Best shfl_xor_best(Best v, int m) {
   return o;
 }
 
+// Chunks go to this many waves (or lanes) in turn.
+constexpr int kChunkWaves = 16;
+
+// The chunk of the largest score (ties: the lower index), as chunk_select's
+// workgroup finds it: sixteen groups of every sixteenth chunk, then the groups
+// in order. Every wave of a workgroup computes it by itself.
+__device__ __forceinline__ int best_chunk(const double* score, int M, int lane) {
+  const int g = lane & (kChunkWaves - 1);
+  Best best{-DBL_MAX, INT32_MAX};
+  for (int c = g; c < M; c += kChunkWaves) {
+    const Best cand{score[c], c};
+    if (best.i == INT32_MAX || before(cand, best)) best = cand;
+  }
+  Best bb{__shfl(best.s, 0), __shfl(best.i, 0)};
+  for (int w = 1; w < kChunkWaves; ++w) {
+    const Best o{__shfl(best.s, w), __shfl(best.i, w)};
+    if (o.i < M && (bb.i >= M || before(o, bb))) bb = o;
+  }
+  return bb.i < M ? bb.i : 0;
+}
+
 // One 1024-thread workgroup per (batch, head).
 constexpr int kSelThreads = 1024;
 
@@ -103,6 +208,21 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
   const int bh = blockIdx.x, b = bh / p.H, h = bh % p.H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
+  // arrival counters of the attention launch that follows
+  for (int i = bh * NT + tid; i < p.n_zero; i += (int)gridDim.x * NT) p.zero[i] = 0;
+
+  // candidates: logical pages [lo, lo + n_c)
+  int lo = 0, n_c = p.n_cand;
+  if (p.chunk_cos) {
+    const int m = best_chunk(p.chunk_cos + (size_t)b * p.M, p.M, lane);
+    const int32_t* cf = p.chunk_first + (size_t)b * (p.M + 1);
+    lo = clampi(cf[m], 0, p.n_cand);
+    n_c = clampi(cf[m + 1], lo, p.n_cand) - lo;
+    if (p.chunk_out && h == 0 && tid == 0) p.chunk_out[b] = m;
+  } else if (p.cand_range) {
+    lo = clampi(p.cand_range[2 * b], 0, p.n_cand);
+    n_c = clampi(p.cand_range[2 * b + 1], lo, p.n_cand) - lo;
+  }
   // mean query of head h: NPART threads per column each sum a contiguous
   // range of the splits (in order), then the parts are added in order
   {
@@ -111,15 +231,15 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     const int k0 = min(p.n_split, part * per), k1 = min(p.n_split, k0 + per);
     const double* src = p.ws_qs + (size_t)b * p.n_split * (p.H * D) + h * D + col;
     double sacc = 0.0;
-    int k = k0;
-    for (; k + 8 <= k1; k += 8) {
-      double x[8];
+    constexpr int B = 10;  // loads in flight (19 splits per thread at 4680 queries, d = 128)
+    for (int k = k0; k < k1; k += B) {
+      double x[B];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = src[(size_t)(k + u) * (p.H * D)];
+      for (int u = 0; u < B; ++u) x[u] = src[(size_t)min(k + u, k1 - 1) * (p.H * D)];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) sacc += x[u];
+      for (int u = 0; u < B; ++u)
+        if (k + u < k1) sacc += x[u];
     }
-    for (; k < k1; ++k) sacc += src[(size_t)k * (p.H * D)];
     qparts[part][col] = sacc;
     __syncthreads();
     if (tid < D) {
@@ -130,9 +250,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     __syncthreads();
   }
 
-  // candidates: logical pages [lo, lo + n_c)
-  const int lo = p.cand_range ? clampi(p.cand_range[2 * b], 0, p.n_cand) : 0;
-  const int n_c = p.cand_range ? clampi(p.cand_range[2 * b + 1], lo, p.n_cand) - lo : p.n_cand;
   // scores: 16 lanes per candidate, DS consecutive dims each, reduced in a
   // fixed butterfly order; U candidates per lane group have their loads in
   // flight together
@@ -239,75 +356,17 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
 // over its elements, added in a fixed pairwise order, then a fixed butterfly
 // across the wave), cosine = dot / (|p| |c|), 0 for a zero norm; then the
 // top-1 by (cosine desc, index asc) over the workgroup.
-constexpr int kChunkWaves = 16;
-
-// Per-lane partial sums of a.b and a.a over E elements: a lane reads VW
-// consecutive floats per access (VW = 4: 16-byte loads) and issues U accesses
-// of each array per round before using them (the pass is latency-bound: one
-// workgroup streams every chunk embedding of its batch entry); the products
-// of a round go to eight fp64 partials in a fixed order.
-template <int VW>
-__device__ __forceinline__ void dot_norm(const float* a, const float* bv, int E, int lane,
-                                         double (&dot)[8], double (&na)[8]) {
-  constexpr int U = VW == 4 ? 4 : 8;
-  const int n = E / VW;
-  for (int g0 = lane; g0 < n; g0 += 64 * U) {
-    float x[U][VW], y[U][VW];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int g = g0 + 64 * u;
-      const bool in = g < n;
-      if constexpr (VW == 4) {
-        const float4 xa = in ? reinterpret_cast<const float4*>(a)[g] : float4{0.f, 0.f, 0.f, 0.f};
-        const float4 ya = in ? reinterpret_cast<const float4*>(bv)[g] : float4{0.f, 0.f, 0.f, 0.f};
-        x[u][0] = xa.x; x[u][1] = xa.y; x[u][2] = xa.z; x[u][3] = xa.w;
-        y[u][0] = ya.x; y[u][1] = ya.y; y[u][2] = ya.z; y[u][3] = ya.w;
-      } else {
-        x[u][0] = in ? a[g] : 0.f;
-        y[u][0] = in ? bv[g] : 0.f;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < VW; ++e) {
-        const int k = (u * VW + e) & 7;
-        dot[k] = fma((double)x[u][e], (double)y[u][e], dot[k]);
-        na[k] = fma((double)x[u][e], (double)x[u][e], na[k]);
-      }
-  }
-}
-
 __global__ __launch_bounds__(64 * kChunkWaves) void chunk_select_kernel(ChunkSelectParams p) {
   __shared__ Best wbest[kChunkWaves];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* pr = p.prompt + (size_t)b * p.E;
-  auto wave_sum = [](double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-    return v;
-  };
-  auto lane_sum = [](const double (&a)[8]) {
-    return ((a[0] + a[4]) + (a[2] + a[6])) + ((a[1] + a[5]) + (a[3] + a[7]));
-  };
-  // 16-byte loads when every row starts 16-byte aligned
-  const bool vec = (p.E & 3) == 0 && ((uintptr_t)p.prompt & 15) == 0 && ((uintptr_t)p.chunks & 15) == 0;
-  auto sums = [&](const float* x, double (&dot)[8], double (&na)[8]) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) dot[k] = na[k] = 0.0;
-    if (vec) dot_norm<4>(x, pr, p.E, lane, dot, na);
-    else dot_norm<1>(x, pr, p.E, lane, dot, na);
-  };
-  double d8[8], n8[8];
-  sums(pr, d8, n8);
-  const double pn = wave_sum(lane_sum(n8));
+  const bool vec = rows_aligned(p.E, p.prompt, p.chunks);
+  double dt, pn, cc;
+  dot_and_norm<4>(pr, pr, p.E, lane, vec, dt, pn);
   Best best{-DBL_MAX, INT32_MAX};
   for (int c = wave; c < p.M; c += kChunkWaves) {
-    sums(p.chunks + ((size_t)b * p.M + c) * p.E, d8, n8);
-    const double dt = wave_sum(lane_sum(d8));
-    const double cc = wave_sum(lane_sum(n8));
-    const double den = sqrt(cc) * sqrt(pn);
-    const Best cand{den > 0.0 ? dt / den : 0.0, c};
+    dot_and_norm<4>(p.chunks + ((size_t)b * p.M + c) * p.E, pr, p.E, lane, vec, dt, cc);
+    const Best cand{cosine(dt, cc, pn), c};
     if (best.i == INT32_MAX || before(cand, best)) best = cand;
   }
   if (lane == 0) wbest[wave] = best;
@@ -334,9 +393,14 @@ hipError_t launch_chunk_select(int B, const ChunkSelectParams& p, hipStream_t s)
 }
 
 hipError_t launch_qsum(int dtype, int B, const QsumParams& qp, hipStream_t s) {
-  const dim3 g1(qp.n_split, B);
-  if (dtype == HSA_DTYPE_BF16) qsum_kernel<uint16_t><<<g1, 256, 0, s>>>(qp);
-  else qsum_kernel<float><<<g1, 256, 0, s>>>(qp);
+  const dim3 g1(qp.n_split + (qp.chunk_cos ? qp.M : 0), B);
+  if (dtype == HSA_DTYPE_BF16) {
+    if (qp.chunk_cos) qsum_kernel<uint16_t, true><<<g1, 256, 0, s>>>(qp);
+    else qsum_kernel<uint16_t, false><<<g1, 256, 0, s>>>(qp);
+  } else {
+    if (qp.chunk_cos) qsum_kernel<float, true><<<g1, 256, 0, s>>>(qp);
+    else qsum_kernel<float, false><<<g1, 256, 0, s>>>(qp);
+  }
   return hipGetLastError();
 }
 

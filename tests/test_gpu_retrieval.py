@@ -132,3 +132,50 @@ def test_paper_page_geometry():
                      wl, case.k_h, rows=rows)
     assert (gpu["sel"] >= 0).sum(-1).tolist() == [[4, 4]]
     compare(gpu, ref, wl, case.k_h, rows=rows)
+
+
+@pytest.mark.parametrize("M,E,dtype,full", [(1, 64, "bf16", True), (17, 517, "bf16", True), (33, 1024, "f32", True),
+                                            (33, 1024, "f32", False), (16, 4, "bf16", True), (40, 4096, "bf16", True)])
+def test_stage1_inside_the_forward_call_agrees_with_the_call_alone(M, E, dtype, full):
+    # chunk scores beside the query sums (odd and 16-byte rows, one to three
+    # chunks per group of sixteen), two chunks with the best embedding (the
+    # lower index wins), and the smallest fp32 workspace (no scratch for the
+    # scores: Stage 1 is a launch of its own)
+    import torch
+    from paper_2609_34606_amd import (HsaLayer, hsa_chunk_select, hsa_forward_retrieval,
+                                      hsa_retrieval_workspace_size)
+    say(f"[case] stage 1 M={M} E={E} {dtype} full={full}")
+    B, H, d, P, n_q = 2, 2, 64, 16, 40
+    wl = SMALL.replace(batch=B, heads=H, head_dim=d, page_size=P, n_q=n_q, n_cand=2 * M, n_cur=1,
+                       k_h=(1, 2), dtype=dtype, seed=83, value_scale=0.35)
+    case = make_case(wl)
+    dev = upload(case)
+    cuda = dev["q"].device
+    g = torch.Generator(device=cuda)
+    g.manual_seed(7)
+    ce = torch.randn((B, M, E), generator=g, device=cuda)
+    pe = torch.randn((B, E), generator=g, device=cuda)
+    ce[0, M // 2] = ce[0, M - 1] = 2.0 * pe[0]
+    cf = torch.arange(0, 2 * M + 1, 2, dtype=torch.int32, device=cuda).repeat(B, 1).contiguous()
+    layer = HsaLayer(B, H, d, P, dev["q"].dtype, cuda, k_pool=dev["k_pool"], v_pool=dev["v_pool"],
+                     page_table=dev["page_table"])
+    layer.fold(0, wl.n_pages)
+    nbytes = hsa_retrieval_workspace_size(layer.cfg, n_q, 2, 1)
+    if not full:  # query sums, selection, candidate ranges
+        nbytes = -(-n_q // 32) * H * d * 8 * B + 256 + 256
+    sel = torch.full((B, H, 2), -7, dtype=torch.int32, device=cuda)
+    chunk = torch.full((B,), -7, dtype=torch.int32, device=cuda)
+    o = torch.empty_like(dev["q"])
+    hsa_forward_retrieval(layer.cfg, dev["q"], n_q, layer.pool, pe, ce, E, M, cf, wl.n_cand, 1,
+                          [1, 2], 2, layer.kv_state, layer.k_state, layer.page_kmean, dev["g_lin"],
+                          dev["g_sp"], o, chunk_out=chunk, sel_out=sel,
+                          ws=torch.empty(nbytes, dtype=torch.uint8, device=cuda))
+    alone = torch.full((B,), -7, dtype=torch.int32, device=cuda)
+    rng = torch.zeros((B, 2), dtype=torch.int32, device=cuda)
+    hsa_chunk_select(layer.cfg, pe, ce, E, M, cf, wl.n_cand, rng, chunk_out=alone)
+    torch.cuda.synchronize()
+    assert chunk.tolist() == alone.tolist() and int(chunk[0]) == M // 2
+    for b in range(B):
+        pages = sel[b][sel[b] >= 0]
+        assert len(pages) == 3 and ((pages // 2) == int(chunk[b])).all()
+    assert np.isfinite(to_host(o)).all()
