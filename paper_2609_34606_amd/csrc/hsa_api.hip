@@ -101,11 +101,18 @@ StatePlan plan_state(const hsa_config_t* c, int n_pages) {
   // folds upw consecutive units. The pass runs two workgroups per CU, i.e.
   // rounds of kStateTargetGroups; the cost model (in 64-key tiles per slot)
   // counts whole rounds, a fixed cost per workgroup (pipeline fill and the
-  // partial-state write) and the reduction of the partial states.
+  // partial-state write) and the traffic of the partial states (64 KB per
+  // workgroup, written and read back). 3 pages of 1560 keys, 12 heads x d128,
+  // append and fold: 40 us with 468 workgroups (what half this reduction cost
+  // chooses), 33 us with 324, 35 us with 180; the 24- and 123-page folds keep
+  // their plans. fp32 tiles take four times the matrix time, which hides more
+  // of that traffic: 19 pages of 392, 8 heads, 194 us with 456 workgroups in a
+  // whole step, 201 us with 304.
   StatePlan best{1, c->page_size, 1, std::max(n_pages, 1)};
   if (n_pages <= 0) return best;
   const long bh = (long)c->batch * c->num_heads;
-  constexpr double kGroupTiles = 2.5, kReduceTilesPerGroup = 0.004;
+  constexpr double kGroupTiles = 2.5;
+  const double kReduceTilesPerGroup = c->dtype == HSA_DTYPE_BF16 ? 0.008 : 0.004;
   double best_cost = 1e300;
   for (int parts = 1; parts <= 16; ++parts) {
     int len = (c->page_size + parts - 1) / parts;
