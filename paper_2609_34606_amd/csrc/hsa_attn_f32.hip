@@ -136,14 +136,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
     total = ld_const(p.blist_len + cell);
     lst = p.blist + cell * p.blist_cap;
   } else {
-    // selected pages: entries before the first one outside [0, max_pages)
-    for (bool more = true; more && n_sel < p.k_max;) {
-      const int i = n_sel + lane;
-      const int e = i < p.k_max ? selrow[i] : -1;
-      const uint64_t stop = __ballot(e < 0 || e >= p.max_pages);
-      more = stop == 0;
-      n_sel += more ? 64 : __builtin_ctzll(stop);
-    }
+    n_sel = count_selected(selrow, p.k_max, p.max_pages, lane);
     total = (n_sel + p.n_cur) * tpp;
   }
   int u = (int)((long)total * seg_a / n_steps);

@@ -99,12 +99,8 @@ struct ListGeom {
 
 __device__ __forceinline__ ListGeom list_geom(const BlockSelParams& p, const int32_t* selrow) {
   ListGeom g;
-  int n = 0;
-  while (n < p.k_max) {
-    const int e = selrow[n];
-    if (e < 0 || e >= p.max_pages) break;
-    ++n;
-  }
+  const int n = __builtin_amdgcn_readfirstlane(
+      count_selected(selrow, p.k_max, p.max_pages, (int)(threadIdx.x & 63)));
   g.n_sel = n;
   g.nbh = (p.P + kBlockHist - 1) / kBlockHist;
   g.nbc = (p.P + kBlockCur - 1) / kBlockCur;

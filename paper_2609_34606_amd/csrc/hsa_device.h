@@ -116,6 +116,18 @@ __device__ __forceinline__ int2 ld_const(const int2* p) {
   return make_int2((int)(uint32_t)v, (int)(uint32_t)(v >> 32));
 }
 
+// Valid entries of a selection row: those before the first one outside
+// [0, max_pages), at most k_max. One load per 64 entries instead of a chain of
+// dependent ones. Every lane of the wave must call it.
+__device__ __forceinline__ int count_selected(const int32_t* row, int k_max, int max_pages, int lane) {
+  for (int n = 0; n < k_max; n += 64) {
+    const int e = row[min(n + lane, k_max - 1)];
+    const uint64_t stop = __ballot(n + lane >= k_max || e < 0 || e >= max_pages);
+    if (stop) return n + __builtin_ctzll(stop);
+  }
+  return k_max;
+}
+
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
 }  // namespace hsa
