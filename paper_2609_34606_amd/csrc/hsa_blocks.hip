@@ -18,9 +18,10 @@
 //   1. block_kmean: one workgroup per (b, h, key block) sums the block's keys
 //      (exact in fp64 for bf16 keys) and writes the mean, d-major.
 //   2. pooled_rows: one workgroup per (b, h, 4 query blocks) scores the
-//      blocks (a thread per key block), then each of four waves takes one
-//      query block: softmax, a bitonic sort (in registers up to 1024 blocks,
-//      else in LDS), the Gini term and the running weight in sorted order.
+//      blocks (fp64 MFMAs), then two waves take each query block: softmax, the
+//      order of its weights (positions counted up to 512 blocks; a bitonic
+//      sort, in registers up to 1024 blocks, else in LDS), the Gini term and
+//      the running weight in that order.
 //   3. block_lists: one workgroup per (b, h, 128-query tile) forms the
 //      threshold from every query block's Gini term (same order in every
 //      workgroup), cuts the two prefixes of its query blocks and writes the
@@ -37,8 +38,7 @@
 namespace hsa {
 namespace {
 
-// threads of a pooled_rows workgroup: one key block per thread in the score
-// loop (up to 512 blocks), then one wave per query block
+// threads of a pooled_rows workgroup: two waves per query block
 constexpr int kRowsThreads = 512;
 
 template <typename T>
@@ -162,6 +162,15 @@ __global__ __launch_bounds__(256) void block_kmean_kernel(BlockSelParams p) {
   }
 }
 
+// (weight a, id ia) ranks before (weight b, id ib): descending weight, then
+// ascending id. Weights are compared as the integers of their bits, which
+// order non-negative doubles (and the -1 of padding, last) as their values do
+// and give NaNs a place too (as values they would let padding into the row).
+__device__ __forceinline__ bool ranks_before(double a, int ia, double b, int ib) {
+  const int64_t ka = __double_as_longlong(a), kb = __double_as_longlong(b);
+  return (ka > kb) | ((ka == kb) & (ia < ib));
+}
+
 // One wave sorts n_pad (weight, id) pairs in LDS into the order (weight
 // descending, id ascending) with a bitonic network. In each stage a lane
 // handles pairs lane + 64c; all of its pairs are read before any is written,
@@ -191,7 +200,7 @@ __device__ void bitonic_sort_wave(double* rp, int32_t* ri, int n_pad, int lane) 
         for (int c = 0; c < PPL; ++c) {
           const int x = x0 + lane + 64 * c;
           if (x < half) {
-            const bool a_first = pa[c] > pb[c] || (pa[c] == pb[c] && ia[c] < ib[c]);
+            const bool a_first = ranks_before(pa[c], ia[c], pb[c], ib[c]);
             if (a_first != ((ii[c] & k) == 0)) {
               rp[ii[c]] = pb[c];
               rp[ii[c] + jj] = pa[c];
@@ -229,7 +238,7 @@ __device__ void bitonic_sort_regs(double* rp, int32_t* ri, int n_pad, int lane) 
           const double tw = __shfl_xor(w[e], m);
           const int ti = __shfl_xor(id[e], m);
           // selects, not branches: every lane takes the same path
-          const bool mine_first = (w[e] > tw) | ((w[e] == tw) & (id[e] < ti));
+          const bool mine_first = ranks_before(w[e], id[e], tw, ti);
           const bool desc = ((lane * E + e) & k) == 0;
           const bool take = (desc != mine_first) == lower;
           w[e] = take ? tw : w[e];
@@ -244,7 +253,7 @@ __device__ void bitonic_sort_regs(double* rp, int32_t* ri, int n_pad, int lane) 
             if (e & jj) continue;
             const double wa = w[e], wb = w[e + jj];
             const int ia = id[e], ib = id[e + jj];
-            const bool a_first = (wa > wb) | ((wa == wb) & (ia < ib));
+            const bool a_first = ranks_before(wa, ia, wb, ib);
             const bool sw = a_first != (((lane * E + e) & k) == 0);
             w[e] = sw ? wb : wa;
             w[e + jj] = sw ? wa : wb;
@@ -264,9 +273,76 @@ __device__ void bitonic_sort_regs(double* rp, int32_t* ri, int n_pad, int lane) 
   wave_sync();
 }
 
+// Position of each of a row's N <= 64 E weights in the order (weight
+// descending, id ascending), counted: lane l holds entries l + 64 e and
+// compares them with every entry j of its share (32 of each 64), read at one
+// LDS address by all lanes. Weights are compared as the integers of their bits,
+// which order non-negative doubles alike and leave NaNs in some order, so the
+// positions are always a permutation. N^2 / 64 compares of two instructions
+// on two waves per row beat the sorting network up to 512 entries: 283 of them
+// 22 us of a launch of 37 for the network (padded to 512), 11 us for this.
+template <int E>
+__device__ __forceinline__ void count_ranks(const double* rp, int N, int lane, int share, int (&cnt)[E]) {
+  const int64_t* key = reinterpret_cast<const int64_t*>(rp);
+  int64_t mine[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    mine[e] = key[min(lane + 64 * e, N - 1)];
+    cnt[e] = 0;
+  }
+#pragma unroll
+  for (int f = 0; f < E; ++f) {
+    const int j0 = 64 * f + 32 * share, j1 = min(N, j0 + 32);
+#pragma unroll 4
+    for (int j = j0; j < j1; ++j) {
+      const int64_t kj = key[j];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        // an equal weight ranks before this entry if its id is lower
+        if (e > f) cnt[e] += kj >= mine[e] ? 1 : 0;
+        else if (e < f) cnt[e] += kj > mine[e] ? 1 : 0;
+        else cnt[e] += kj > mine[e] - (j - 64 * f < lane ? 1 : 0) ? 1 : 0;
+      }
+    }
+  }
+}
+
+// The row's weights and ids in that order, in place: waves with share 0 and 1
+// of a row call it alike; every wave of the workgroup meets its two barriers
+// (active: this wave has a row).
+template <int E>
+__device__ __forceinline__ void rank_order(double* rp, int32_t* ri, int N, int lane, int share, bool active) {
+  int cnt[E];
+  if (active) {
+    count_ranks<E>(rp, N, lane, share, cnt);
+    if (share == 1)
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        if (lane + 64 * e < N) ri[lane + 64 * e] = cnt[e];
+  }
+  __syncthreads();
+  if (active && share == 0) {
+    double w[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = min(lane + 64 * e, N - 1);
+      cnt[e] += ri[i];
+      w[e] = rp[i];
+    }
+    wave_sync();
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+      if (lane + 64 * e < N) {
+        rp[cnt[e]] = w[e];
+        ri[cnt[e]] = lane + 64 * e;
+      }
+    wave_sync();
+  }
+}
+
 // ---------------------------------------------------------------- 2. pooled rows
-// p.rpg query blocks per workgroup (1..4, one per wave of the first four;
-// fewer for long lists so that the rows fit in LDS).
+// p.rpg query blocks per workgroup (1..4, two waves each; fewer for long lists
+// so that the rows fit in LDS).
 template <int D>
 __global__ __launch_bounds__(kRowsThreads) void pooled_rows_kernel(BlockSelParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t dsm[];
@@ -296,74 +372,88 @@ __global__ __launch_bounds__(kRowsThreads) void pooled_rows_kernel(BlockSelParam
     qbar[i * D + dd] = v;
   }
   __syncthreads();
-  // scaled scores of the key blocks against the group's query blocks (rows
-  // past rpg read row 0's mean and are not stored)
-  const double* kb = p.kbar_t + bh * D * p.n_blk_max;
-  int qi[4];
+  // Scaled scores of the key blocks against the group's query blocks on the
+  // fp64 matrix instruction (16x16x4, query blocks as rows, of which rpg <= 4
+  // are real): a wave takes 16 key blocks at a time, all of a tile's
+  // block-mean loads in flight. A thread per key block, its query-block value
+  // read from LDS for every FMA, took 8 us of a launch of 22 (7 pages of 1560
+  // keys per head, 12 heads, 4680 queries).
+  // Lane l: A row and B column l % 16, k = 4 c + l / 16; register r of the
+  // result is row l / 16 + 4 r, column l % 16.
+  {
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    constexpr int NS = D / 4;
+    const double* kb = p.kbar_t + bh * D * p.n_blk_max;
+    const int l16 = lane & 15, g = lane >> 4;
+    double qa[NS];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) qi[i] = (i < rpg ? i : 0) * D;
-  for (int j = tid; j < N; j += kRowsThreads) {
-    double a[4] = {0, 0, 0, 0};
-    // 32 block-mean loads in flight before their FMAs (the sums keep the
-    // order dd = 0, 1, ...)
-    for (int d0 = 0; d0 < D; d0 += 32) {
-      double kv[32];
+    for (int c = 0; c < NS; ++c) qa[c] = l16 < rpg ? qbar[l16 * D + 4 * c + g] : 0.0;
+    for (int j0 = 16 * wave; j0 < N; j0 += 16 * (kRowsThreads / 64)) {
+      const int j = min(j0 + l16, N - 1);
+      double kv[NS];
 #pragma unroll
-      for (int u = 0; u < 32; ++u) kv[u] = kb[(size_t)(d0 + u) * p.n_blk_max + j];
+      for (int c = 0; c < NS; ++c) kv[c] = kb[(size_t)(4 * c + g) * p.n_blk_max + j];
+      f64x4 acc = f64x4{0};
 #pragma unroll
-      for (int u = 0; u < 32; ++u)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = fma(qbar[qi[i] + d0 + u], kv[u], a[i]);
+      for (int c = 0; c < NS; ++c) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[c], kv[c], acc, 0, 0, 0);
+      if (g < rpg && j0 + l16 < N) rowp[g * p.n_pad + j0 + l16] = acc[0] * p.scale;
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (i < rpg) rowp[i * p.n_pad + j] = a[i] * p.scale;
   }
   __syncthreads();
 
-  // one query block per wave from here on
-  const int qb = qb0 + wave;
-  if (wave >= rpg || qb >= p.n_qb) return;
+  // Query block qb0 + r on wave r from here on; wave r + 4 helps to order it.
+  const int r_own = wave & 3, share = wave >> 2;
+  const int qb = qb0 + r_own;
+  const bool active = r_own < rpg && qb < p.n_qb;
   const size_t row = bh * p.n_qb + qb;
   if (N == 0) {
+    if (!active || share) return;
     if (lane == 0) p.row_g[row] = 0.0;
     if (p.pooled)
       for (int j = lane; j < p.kept_len; j += 64) p.pooled[row * p.kept_len + j] = 0.0;
     return;
   }
-  double* rp = rowp + wave * p.n_pad;
-  int32_t* ri = rowi + wave * p.n_pad;
-  double mx = -INFINITY;
-  for (int j = lane; j < N; j += 64) mx = fmax(mx, rp[j]);
-  mx = wave_max(mx);
-  double z = 0.0;
-  for (int j = lane; j < N; j += 64) {
-    const double e = exp(rp[j] - mx);
-    rp[j] = e;
-    z += e;
+  double* rp = rowp + (active ? r_own : 0) * p.n_pad;
+  int32_t* ri = rowi + (active ? r_own : 0) * p.n_pad;
+  const bool network = N > 512;
+  if (active && share == 0) {
+    double mx = -INFINITY;
+    for (int j = lane; j < N; j += 64) mx = fmax(mx, rp[j]);
+    mx = wave_max(mx);
+    double z = 0.0;
+    for (int j = lane; j < N; j += 64) {
+      const double e = exp(rp[j] - mx);
+      rp[j] = e;
+      z += e;
+    }
+    z = wave_sum(z);
+    for (int j = lane; j < N; j += 64) rp[j] = rp[j] / z;
+    if (network)
+      for (int j = lane; j < p.n_pad; j += 64) {
+        if (j >= N) rp[j] = -1.0;  // padding sorts after every weight
+        ri[j] = j < N ? j : INT_MAX;
+      }
+    if (p.pooled)
+      for (int j = lane; j < p.kept_len; j += 64) p.pooled[row * p.kept_len + j] = j < N ? rp[j] : 0.0;
   }
-  z = wave_sum(z);
-  for (int j = lane; j < p.n_pad; j += 64) {
-    if (j < N) {
-      const double pj = rp[j] / z;
-      rp[j] = pj;
-      ri[j] = j;
-    } else {
-      rp[j] = -1.0;  // padding sorts after every weight
-      ri[j] = INT_MAX;
+  __syncthreads();
+  // order: weight descending, block id ascending
+  if (!network) {
+    switch ((N + 63) / 64) {
+      case 1: rank_order<1>(rp, ri, N, lane, share, active); break;
+      case 2: rank_order<2>(rp, ri, N, lane, share, active); break;
+      case 3: rank_order<3>(rp, ri, N, lane, share, active); break;
+      case 4: rank_order<4>(rp, ri, N, lane, share, active); break;
+      case 5: rank_order<5>(rp, ri, N, lane, share, active); break;
+      case 6: rank_order<6>(rp, ri, N, lane, share, active); break;
+      case 7: rank_order<7>(rp, ri, N, lane, share, active); break;
+      default: rank_order<8>(rp, ri, N, lane, share, active);
     }
   }
-  if (p.pooled)
-    for (int j = lane; j < p.kept_len; j += 64) p.pooled[row * p.kept_len + j] = j < N ? rp[j] : 0.0;
-  wave_sync();
-  // sort: weight descending, block id ascending
-  switch (p.n_pad) {
-    case 64: bitonic_sort_regs<1>(rp, ri, p.n_pad, lane); break;
-    case 128: bitonic_sort_regs<2>(rp, ri, p.n_pad, lane); break;
-    case 256: bitonic_sort_regs<4>(rp, ri, p.n_pad, lane); break;
-    case 512: bitonic_sort_regs<8>(rp, ri, p.n_pad, lane); break;
-    case 1024: bitonic_sort_regs<16>(rp, ri, p.n_pad, lane); break;
-    default: bitonic_sort_wave<8>(rp, ri, p.n_pad, lane);
+  if (!active || share) return;
+  if (network) {
+    if (p.n_pad == 1024) bitonic_sort_regs<16>(rp, ri, p.n_pad, lane);
+    else bitonic_sort_wave<8>(rp, ri, p.n_pad, lane);
   }
   // Gini term: (1/N) sum over sorted positions m = pos + 1 of (N - 2m + 1) p
   double gs = 0.0;
@@ -372,7 +462,7 @@ __global__ __launch_bounds__(kRowsThreads) void pooled_rows_kernel(BlockSelParam
   if (lane == 0) p.row_g[row] = gs;
   // running weight in sorted order: each lane a contiguous run, then a scan
   // of the run totals across the wave
-  const int E = p.n_pad / 64;
+  const int E = (N + 63) / 64;
   const int r0 = lane * E;
   double tot = 0.0;
   for (int r = 0; r < E; ++r)

@@ -238,3 +238,56 @@ def test_c3_zero_threshold_full_size():
     splits of a query block then walk no tile at all, and the merge has to
     weigh their empty partials out."""
     _full_size("c3", qb_k=4, tau=(0.0, 0.0))
+
+
+@pytest.mark.parametrize("N", [1, 63, 64, 65, 200, 449, 512, 513, 1030])
+@pytest.mark.parametrize("d", [64, 128])
+def test_row_order_with_ties_and_nan(N, d):
+    # One 64-key current page per key block, so N blocks: the counted order
+    # (up to 512) and the sorting networks above it, on either side of each
+    # wave's share of 64. Pages repeat, so weights tie exactly and the lower
+    # block id has to come first. The kept prefix must be the head of a stable
+    # sort of the library's own weights, and every row a permutation; a query
+    # block of NaN keeps every block once.
+    import torch
+    from paper_2609_34606_amd import config, hsa_block_select, kv_pool
+    say(f"[case] row order N={N} d={d}")
+    P, H, n_q = 64, 2, 200                      # four query blocks, the last ragged
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(9)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda:0")
+    base = rnd(max(1, N // 3), H, P, d).to(torch.bfloat16)
+    k_pool = base[torch.arange(N, device="cuda:0") % base.shape[0]].contiguous()
+    v_pool = torch.zeros((N, H, d, P), dtype=torch.bfloat16, device="cuda:0")
+    table = torch.arange(N, dtype=torch.int32, device="cuda:0")[None].contiguous()
+    q = (4.0 * rnd(1, n_q, H, d)).to(torch.bfloat16)
+    cfg = config(1, H, d, P, torch.bfloat16)
+    for nan in (False, True):
+        if nan:
+            q[0, 70, 1, 3] = float("nan")        # query block 1 of head 1
+        n_kept = torch.zeros((1, H, 4), dtype=torch.int32, device="cuda:0")
+        kept = torch.full((1, H, 4, N), -7, dtype=torch.int32, device="cuda:0")
+        pooled = torch.zeros((1, H, 4, N), dtype=torch.float64, device="cuda:0")
+        if N > 1024:                             # pages of one list are limited
+            k2, v2 = k_pool[:N // 2 * 2], v_pool[:N // 2 * 2]
+            c2 = config(1, H, d, 2 * P, torch.bfloat16)
+            kk = k2.reshape(N // 2, 2, H, P, d).transpose(1, 2).reshape(N // 2, H, 2 * P, d).contiguous()
+            vv = torch.zeros((N // 2, H, d, 2 * P), dtype=torch.bfloat16, device="cuda:0")
+            t2 = table[:, :N // 2].contiguous()
+            hsa_block_select(c2, q, n_q, kv_pool(kk, vv, t2, c2), None, 0, 0, N // 2, n_kept=n_kept,
+                             kept=kept, pooled=pooled, kept_len=N)
+        else:
+            hsa_block_select(cfg, q, n_q, kv_pool(k_pool, v_pool, table, cfg), None, 0, 0, N,
+                             n_kept=n_kept, kept=kept, pooled=pooled, kept_len=N)
+        torch.cuda.synchronize()
+        w, ids, cnt = pooled.cpu().numpy(), kept.cpu().numpy(), n_kept.cpu().numpy()
+        for h in range(H):
+            for i in range(4):
+                n = int(cnt[0, h, i])
+                if nan and h == 1:               # the head's threshold is NaN: every block
+                    assert sorted(ids[0, h, i, :n].tolist()) == list(range(N)), (h, i)
+                    continue
+                want = np.argsort(-w[0, h, i], kind="stable")
+                assert 1 <= n <= N
+                np.testing.assert_array_equal(ids[0, h, i, :n], want[:n])
+                assert (ids[0, h, i, n:] == -1).all()
