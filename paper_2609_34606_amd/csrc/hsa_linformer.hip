@@ -241,7 +241,9 @@ __global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_
         } else if (part_out) {
           *reinterpret_cast<f32x4*>(part_out + R * D + d * R + j) = v;
         } else {
-          *reinterpret_cast<u32x2*>(cv + d * R + j) = u32x2{pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
+          // (one 8-byte store at an element's alignment)
+          typedef uint32_t u32x2e __attribute__((ext_vector_type(2), aligned(2)));
+          *reinterpret_cast<u32x2e*>(cv + d * R + j) = u32x2e{pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
         }
       }
     }
