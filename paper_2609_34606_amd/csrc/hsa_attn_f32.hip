@@ -294,13 +294,15 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
       mx = fmaxf(mx, __shfl_xor(mx, 32));
       const bool grow = mx * c2 > m_run * c2 + 8.f;
       const float m_new = grow ? mx : m_run;
-      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c2);
+      const float alpha = grow ? __builtin_amdgcn_exp2f((m_run - m_new) * c2) : 1.f;
       l_run *= alpha;
 #pragma unroll
       for (int m = 0; m < NM; ++m) acc[m] *= alpha;
       m_run = m_new;
     }
-    const float mc = m_run * c2;
+    // (finite while every score of the query so far is -inf: their weights are
+    // zeros, where -inf less a reference of -inf would be NaN)
+    const float mc = fmaxf(m_run * c2, -FLT_MAX);
     float pv[2][4];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
