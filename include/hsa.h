@@ -245,6 +245,8 @@ hsa_status_t hsa_page_select(const hsa_config_t* cfg, const void* q, int32_t n_q
  * KV construction", here a virtual concatenation through the page table).
  *   o_sp[b][i][h] = sum_j softmax_j(scale * q_i . k_j) v_j   (fp32)
  *   lse[b][h][i]  = log sum_j exp(scale * q_i . k_j)          (nullable)
+ * A key whose score is -inf has no weight; a query with no other keys gets
+ * o_sp = 0 and lse = -inf.
  * k_h: host int32 [H], upper bounds on the valid entries of each sel row
  * (used for scheduling only; may be NULL meaning k_max). A head whose active
  * set is empty is an error only if n_cur_pages == 0 and k_max == 0

@@ -508,8 +508,8 @@ __global__ __launch_bounds__(64 * kW, 8 / kW) void attn_bf16_kernel(AttnParams p
   f32x16 acc[NM];
 #pragma unroll
   for (int m = 0; m < NM; ++m) acc[m] = f32x16{0};
-  float m_run = -INFINITY, l_run = 0.f;
   const float c2 = p.scale_log2;
+  float m_run = softmax_floor(c2), l_run = 0.f;
   const int krow = key_perm(l32);
 
   // prologue: K(0), V(0), K(1). The entries of the tile being computed (ec),
@@ -883,8 +883,8 @@ __global__ __launch_bounds__(512, 1) void attn_pp_kernel(AttnParams p_arg) {
   f32x16 acc[NM];
 #pragma unroll
   for (int m = 0; m < NM; ++m) acc[m] = f32x16{0};
-  float m_run = -INFINITY, l_run = 0.f;
   const float c2 = p.scale_log2;
+  float m_run = softmax_floor(c2), l_run = 0.f;
   const int krow = key_perm(l32);
 
   // The lane's byte offsets of its MFMA operands within a tile are fixed:

@@ -239,8 +239,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
   f32x4 acc[NM];
 #pragma unroll
   for (int m = 0; m < NM; ++m) acc[m] = f32x4{0};
-  float m_run = -INFINITY, l_run = 0.f;
   const float c2 = p.scale_log2;
+  float m_run = softmax_floor(c2), l_run = 0.f;
 
   // keys lo..hi-1 of the window in LDS buffer buf
   auto compute = [&](int buf, int lo, int hi) {
@@ -294,15 +294,13 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
       mx = fmaxf(mx, __shfl_xor(mx, 32));
       const bool grow = mx * c2 > m_run * c2 + 8.f;
       const float m_new = grow ? mx : m_run;
-      const float alpha = grow ? __builtin_amdgcn_exp2f((m_run - m_new) * c2) : 1.f;
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c2);
       l_run *= alpha;
 #pragma unroll
       for (int m = 0; m < NM; ++m) acc[m] *= alpha;
       m_run = m_new;
     }
-    // (finite while every score of the query so far is -inf: their weights are
-    // zeros, where -inf less a reference of -inf would be NaN)
-    const float mc = fmaxf(m_run * c2, -FLT_MAX);
+    const float mc = m_run * c2;
     float pv[2][4];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
@@ -358,8 +356,8 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
     lds_barrier();
     const float m_o = in[0], l_o = in[64];
     m_tot = fmaxf(m_run, m_o);
-    const float w = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_tot) * c2);
-    const float w_o = m_o == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_o - m_tot) * c2);
+    const float w = __builtin_amdgcn_exp2f((m_run - m_tot) * c2);
+    const float w_o = __builtin_amdgcn_exp2f((m_o - m_tot) * c2);
     const float w0 = s ? w_o : w, w1 = s ? w : w_o;   // weights of streams 0 and 1
     l_tot = s ? fmaf(w0, l_o, w1 * l_run) : fmaf(w0, l_run, w1 * l_o);
 #pragma unroll
@@ -427,7 +425,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
 #pragma unroll
       for (int j = 0; j < kB; ++j) {
         if (k + j >= np) break;
-        const float w = m4[j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m4[j] - m_tot) * c2);
+        const float w = __builtin_amdgcn_exp2f((m4[j] - m_tot) * c2);
         l_tot = fmaf(w, l4[j], l_tot);
 #pragma unroll
         for (int i = 0; i < 4 * NH; ++i) oa[i / 4][i % 4] = fmaf(w, v[j][i], oa[i / 4][i % 4]);

@@ -1,6 +1,7 @@
 // Device-side helpers shared by the HSA kernels (gfx950 / CDNA4 only).
 #pragma once
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -127,6 +128,12 @@ __device__ __forceinline__ int count_selected(const int32_t* row, int k_max, int
   }
   return k_max;
 }
+
+// Where an online softmax's reference maximum (raw score units) starts: the
+// lowest float, so that scores of -inf, and whole tiles of them, get zero
+// weights (a start of -inf makes -inf less -inf, NaN, of such a tile). For a
+// scale c2 above 1 it is raised so that the scaled reference stays finite.
+__device__ __forceinline__ float softmax_floor(float c2) { return c2 > 1.f ? -0.5f * FLT_MAX / c2 : -FLT_MAX; }
 
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 

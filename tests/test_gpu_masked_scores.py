@@ -43,11 +43,11 @@ def _inputs(r, H, d, n_q, P, n_pages, mask, kind):
     return q, k, v, m
 
 
-def _reference(q, k, v, m):
+def _reference(q, k, v, m, scale=0.0):
     q, k, v = q.astype(np.float64), k.astype(np.float64), v.astype(np.float64)
     k0 = np.where(np.isinf(k[:, :, :1]), 0.0, k[:, :, :1])
     k = np.concatenate([k0 * 0.0, k[:, :, 1:]], axis=2)  # channel 0 only masks
-    s = np.einsum("qhd,hkd->hqk", q, k) / np.sqrt(q.shape[-1])
+    s = np.einsum("qhd,hkd->hqk", q, k) * (scale or q.shape[-1] ** -0.5)
     s = np.where(m[None], -np.inf, s)
     mx = s.max(-1, keepdims=True)
     e = np.exp(s - np.where(np.isinf(mx), 0.0, mx))
@@ -57,7 +57,7 @@ def _reference(q, k, v, m):
         return o, np.log(z[..., 0]) + np.where(np.isinf(mx), 0.0, mx)[..., 0]
 
 
-def _run(dtype, q, k, v, P, ws_bytes=None):
+def _run(dtype, q, k, v, P, ws_bytes=None, scale=0.0):
     import torch
     from paper_2609_34606_amd import HsaLayer, hsa_sparse_attn, hsa_sparse_attn_workspace_size
     n_q, H, d = q.shape
@@ -67,7 +67,8 @@ def _run(dtype, q, k, v, P, ws_bytes=None):
     kp = k.reshape(H, n_pages, P, d).transpose(1, 0, 2, 3)
     vp = v.reshape(H, n_pages, P, d).transpose(1, 0, 3, 2)
     layer = HsaLayer(1, H, d, P, dt, "cuda:0", k_pool=up(kp), v_pool=up(vp),
-                     page_table=torch.arange(n_pages, dtype=torch.int32, device="cuda:0")[None])
+                     page_table=torch.arange(n_pages, dtype=torch.int32, device="cuda:0")[None],
+                     sm_scale=scale)
     o = torch.full((1, n_q, H, d), float("nan"), dtype=torch.float32, device="cuda:0")
     lse = torch.full((1, H, n_q), float("nan"), dtype=torch.float32, device="cuda:0")
     nbytes = hsa_sparse_attn_workspace_size(layer.cfg, n_q, 0, n_pages) if ws_bytes is None else ws_bytes
@@ -78,9 +79,10 @@ def _run(dtype, q, k, v, P, ws_bytes=None):
 
 
 # fp32: items cut into pieces with the workspace of the size query, whole with
-# none
+# none; bf16: 33 tiles of one item are cut into two ranges, 8 are not
 @pytest.mark.parametrize("dtype,d,n_q,P,n_pages,ws_bytes", [
-    ("f32", 64, 70, 40, 9, None), ("f32", 128, 70, 392, 5, None), ("f32", 128, 70, 392, 5, 0)])
+    ("f32", 64, 70, 40, 9, None), ("f32", 128, 70, 392, 5, None), ("f32", 128, 70, 392, 5, 0),
+    ("bf16", 64, 300, 128, 4, None), ("bf16", 128, 70, 200, 8, None), ("bf16", 128, 70, 40, 33, None)])
 @pytest.mark.parametrize("kind", ["inf", "overflow"])
 @pytest.mark.parametrize("mask", ["first", "odd", "middle", "most"])
 def test_masked_keys_get_no_weight(dtype, d, n_q, P, n_pages, ws_bytes, kind, mask):
@@ -92,14 +94,15 @@ def test_masked_keys_get_no_weight(dtype, d, n_q, P, n_pages, ws_bytes, kind, ma
     np.testing.assert_allclose(lse, ref_lse, atol=2e-3 if dtype == "bf16" else 1e-4)
 
 
-@pytest.mark.parametrize("dtype,P,n_pages", [("f32", 392, 5)])
-def test_a_query_with_no_weights(dtype, P, n_pages):
+@pytest.mark.parametrize("dtype,P,n_pages", [("f32", 392, 5), ("bf16", 40, 33)])
+@pytest.mark.parametrize("scale", [0.0, 0.75])  # 0.75 log2(e) > 1: a lower starting reference
+def test_a_query_with_no_weights(dtype, P, n_pages, scale):
     # every score of two thirds of the queries is -inf: zeros and an LSE of
     # -inf, as for an empty list; the other queries are not touched
-    say(f"[case] no weights {dtype} P={P}")
-    q, k, v, m = _inputs(np.random.default_rng(92), 2, 128, 70, P, n_pages, "all", "overflow")
-    o, lse = _run(dtype, q, k, v, P)
-    ref_o, ref_lse = _reference(q, k, v, m)
+    say(f"[case] no weights {dtype} P={P} scale={scale}")
+    q, k, v, m = _inputs(np.random.default_rng(92), 2, 64, 70, P, n_pages, "all", "overflow")
+    o, lse = _run(dtype, q, k, v, P, scale=scale)
+    ref_o, ref_lse = _reference(q, k, v, m, scale)
     none = m.all(1)
     assert (o[none] == 0).all() and np.isneginf(lse[:, none]).all()
     assert_close("O_sp", o[~none], ref_o[~none], **(BF16_TOL if dtype == "bf16" else F32_TOL))
