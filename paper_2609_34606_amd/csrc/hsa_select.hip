@@ -9,6 +9,7 @@
 // order (repeated block-wide arg-max for very long lists), so equal scores
 // keep the older page.
 #include <float.h>
+#include <type_traits>
 
 #include "hsa_device.h"
 #include "hsa_kernels.h"
@@ -190,10 +191,11 @@ __device__ __forceinline__ int best_chunk(const double* score, int M, int lane) 
   return bb.i < M ? bb.i : 0;
 }
 
-// One 1024-thread workgroup per (batch, head).
+// One 1024-thread workgroup per (batch, head). kStage1: the candidates are the
+// pages of the best chunk (compiled apart: the test alone cost 0.2 us).
 constexpr int kSelThreads = 1024;
 
-template <int D>
+template <int D, bool kStage1>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
   constexpr int NT = kSelThreads, NW = NT / 64;
   constexpr int DS = D / 16;       // d values per lane when 16 lanes share a candidate
@@ -208,12 +210,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
   const int bh = blockIdx.x, b = bh / p.H, h = bh % p.H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-  // arrival counters of the attention launch that follows
-  for (int i = bh * NT + tid; i < p.n_zero; i += (int)gridDim.x * NT) p.zero[i] = 0;
-
   // candidates: logical pages [lo, lo + n_c)
   int lo = 0, n_c = p.n_cand;
-  if (p.chunk_cos) {
+  if (kStage1) {
     const int m = best_chunk(p.chunk_cos + (size_t)b * p.M, p.M, lane);
     const int32_t* cf = p.chunk_first + (size_t)b * (p.M + 1);
     lo = clampi(cf[m], 0, p.n_cand);
@@ -230,15 +229,28 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     const int per = (p.n_split + NPART - 1) / NPART;
     const int k0 = min(p.n_split, part * per), k1 = min(p.n_split, k0 + per);
     const double* src = p.ws_qs + (size_t)b * p.n_split * (p.H * D) + h * D + col;
+    // in batches whose loads are in flight together: ten while more than four
+    // splits are left (19 per thread at 4680 queries, d = 128), else the least
+    // that holds them. Kernel times at one candidate list of 13 (before: eight
+    // at a time, then one by one; ten always): 256 queries 5.4, 6.7, now 5.5
+    // us; 1560: 7.2, 6.6, 6.4; 3000: 7.3, 7.8, 6.9; 4680: 8.2, 8.1, 8.0.
     double sacc = 0.0;
-    constexpr int B = 10;  // loads in flight (19 splits per thread at 4680 queries, d = 128)
-    for (int k = k0; k < k1; k += B) {
+    int k = k0;
+    auto sum = [&](auto batch) {
+      constexpr int B = decltype(batch)::value;
       double x[B];
 #pragma unroll
       for (int u = 0; u < B; ++u) x[u] = src[(size_t)min(k + u, k1 - 1) * (p.H * D)];
 #pragma unroll
       for (int u = 0; u < B; ++u)
         if (k + u < k1) sacc += x[u];
+      k += B;
+    };
+    while (k < k1) {
+      if (k1 - k == 1) sum(std::integral_constant<int, 1>{});
+      else if (k1 - k == 2) sum(std::integral_constant<int, 2>{});
+      else if (k1 - k <= 4) sum(std::integral_constant<int, 4>{});
+      else sum(std::integral_constant<int, 10>{});
     }
     qparts[part][col] = sacc;
     __syncthreads();
@@ -249,6 +261,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     }
     __syncthreads();
   }
+
+  // arrival counters of the attention launch that follows (here: ahead of the
+  // mean query it delays the sums by 0.2 us)
+  for (int i = bh * NT + tid; i < p.n_zero; i += (int)gridDim.x * NT) p.zero[i] = 0;
 
   // scores: 16 lanes per candidate, DS consecutive dims each, reduced in a
   // fixed butterfly order; U candidates per lane group have their loads in
@@ -409,8 +425,13 @@ hipError_t launch_page_select(int dtype, int d, int B, const QsumParams& qp,
   hipError_t e = launch_qsum(dtype, B, qp, s);
   if (e != hipSuccess) return e;
   const dim3 g2(B * sp.H);
-  if (d == 128) select_kernel<128><<<g2, kSelThreads, 0, s>>>(sp);
-  else select_kernel<64><<<g2, kSelThreads, 0, s>>>(sp);
+  if (sp.chunk_cos) {
+    if (d == 128) select_kernel<128, true><<<g2, kSelThreads, 0, s>>>(sp);
+    else select_kernel<64, true><<<g2, kSelThreads, 0, s>>>(sp);
+  } else {
+    if (d == 128) select_kernel<128, false><<<g2, kSelThreads, 0, s>>>(sp);
+    else select_kernel<64, false><<<g2, kSelThreads, 0, s>>>(sp);
+  }
   return hipGetLastError();
 }
 

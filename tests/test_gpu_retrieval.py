@@ -179,3 +179,28 @@ def test_stage1_inside_the_forward_call_agrees_with_the_call_alone(M, E, dtype, 
         pages = sel[b][sel[b] >= 0]
         assert len(pages) == 3 and ((pages // 2) == int(chunk[b])).all()
     assert np.isfinite(to_host(o)).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q", [1, 257, 600, 1000, 1025, 2560, 2600, 3600])
+def test_mean_query_of_any_split_count(d, n_q):
+    # 1, 2, 3, 4, 5, 10, 11 and 15 partial sums per thread of the selection at
+    # d = 128 (half of it at d = 64): every batch of them, full and partial.
+    # Scores are fp64 sums in another order than numpy's.
+    import torch
+    from paper_2609_34606_amd import config, hsa_page_select
+    say(f"[case] page selection d={d} n_q={n_q}")
+    r = np.random.default_rng(87)
+    H, n_cand = 2, 9
+    q = torch.from_numpy(r.standard_normal((1, n_q, H, d)).astype(np.float32)).to("cuda:0")
+    mean = r.standard_normal((1, H, n_cand, d))
+    cfg = config(1, H, d, 8, torch.float32)
+    sel = torch.full((1, H, n_cand), -7, dtype=torch.int32, device="cuda:0")
+    score = torch.zeros((1, H, n_cand), dtype=torch.float64, device="cuda:0")
+    hsa_page_select(cfg, q, n_q, torch.from_numpy(mean).to("cuda:0"), n_cand, n_cand, [n_cand] * H,
+                    n_cand, sel, sel_score=score)
+    torch.cuda.synchronize()
+    alpha = np.matmul(mean[0], to_host(q).astype(np.float64).mean(1)[0][:, :, None])[:, :, 0] / np.sqrt(d)
+    order = np.argsort(-alpha, axis=1, kind="stable")
+    np.testing.assert_array_equal(to_host(sel)[0], order)
+    np.testing.assert_allclose(to_host(score)[0], np.take_along_axis(alpha, order, 1), rtol=1e-12, atol=1e-15)
