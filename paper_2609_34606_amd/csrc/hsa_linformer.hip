@@ -37,6 +37,10 @@ constexpr int kRow = kT * 2;    // bytes per LDS row: 64 bf16 tokens
 // logical chunk land on distinct bank groups.
 __device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 4)) & 7; }
 
+// Four outputs in one 8-byte store at an element's alignment: nothing more is
+// asked of ck and cv.
+typedef uint32_t u32x2e __attribute__((ext_vector_type(2), aligned(2)));
+
 template <int D, int R>
 struct CompressSmem {
   uint8_t x[D * kRow];     // K^T or V tile [d][64 tokens]
@@ -241,8 +245,6 @@ __global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_
         } else if (part_out) {
           *reinterpret_cast<f32x4*>(part_out + R * D + d * R + j) = v;
         } else {
-          // (one 8-byte store at an element's alignment)
-          typedef uint32_t u32x2e __attribute__((ext_vector_type(2), aligned(2)));
           *reinterpret_cast<u32x2e*>(cv + d * R + j) = u32x2e{pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
         }
       }
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(256) void compress_reduce_kernel(CompressParams p) 
   for (int k = 1; k < p.parts; ++k) s += *reinterpret_cast<const f32x4*>(src + (size_t)k * 2 * RD + e);
   uint16_t* dst = (e < RD ? static_cast<uint16_t*>(p.ck) + hb * RD + e
                           : static_cast<uint16_t*>(p.cv) + hb * RD + (e - RD));
-  *reinterpret_cast<u32x2*>(dst) = u32x2{pack_bf16(s.x, s.y), pack_bf16(s.z, s.w)};
+  *reinterpret_cast<u32x2e*>(dst) = u32x2e{pack_bf16(s.x, s.y), pack_bf16(s.z, s.w)};
 }
 
 // fp32 inputs: plain VALU products, fp32 accumulation in token order (small

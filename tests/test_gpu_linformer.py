@@ -112,6 +112,27 @@ def test_small_ragged_bf16(d, rank):
     _run(SMALL.replace(head_dim=d), rank=rank)
 
 
+@pytest.mark.parametrize("n_pages,parts", [(1, True), (86, False)])
+def test_compressed_pages_at_an_odd_element(n_pages, parts):
+    # ck and cv one element past an aligned address: pages summed from parts
+    # (3 pairs of page and head) and written whole (258 of them)
+    import torch
+    from paper_2609_34606_amd import hsa_linformer_compress_workspace_size
+    wl = SMALL.replace(n_cand=n_pages, n_cur=0, seed=72)
+    say(f"[case] compressed pages at an odd element {wl}")
+    case = make_case(wl)
+    host = dict(k_pool=case.k_pool, v_pool=case.v_pool, page_table=case.page_table)
+    e_k, e_v = make_projections(wl, 64, "gaussian")
+    layer = _layer(wl, upload(case), e_k, e_v)
+    assert (hsa_linformer_compress_workspace_size(layer.cfg, 64, n_pages) > 0) == parts
+    shifted = lambda t: torch.full((t.numel() + 1,), float("nan"), dtype=t.dtype, device=t.device)[1:].view(t.shape)
+    layer.ck, layer.cv = shifted(layer.ck), shifted(layer.cv)
+    assert layer.ck.data_ptr() % 4 == 2 and layer.cv.data_ptr() % 4 == 2
+    layer.compress(0, n_pages)
+    torch.cuda.synchronize()
+    _check_compressed(layer, host, e_k, e_v, wl, sorted({0, n_pages // 2, n_pages - 1}))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_elementwise_gates_linformer(dtype):
     wl = SMALL.replace(dtype=dtype, seed=26)
