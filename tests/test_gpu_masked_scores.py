@@ -15,6 +15,7 @@ MASKS = {
     "odd": lambda i, n: i // 32 % 2 == 1,                # every second 32-key tile
     "middle": lambda i, n: (i >= n // 4) & (i < n - 8),  # first tiles of later pieces
     "most": lambda i, n: i < n - 8,                      # all but eight keys
+    "blocks": lambda i, n: (i >= 128) & (i < 256) | (i >= n - 64),
     "all": lambda i, n: i >= 0,
 }
 
@@ -57,9 +58,10 @@ def _reference(q, k, v, m, scale=0.0):
         return o, np.log(z[..., 0]) + np.where(np.isinf(mx), 0.0, mx)[..., 0]
 
 
-def _run(dtype, q, k, v, P, ws_bytes=None, scale=0.0):
+def _run(dtype, q, k, v, P, ws_bytes=None, scale=0.0, adaptive=False):
     import torch
-    from paper_2609_34606_amd import HsaLayer, hsa_sparse_attn, hsa_sparse_attn_workspace_size
+    from paper_2609_34606_amd import (HsaLayer, hsa_sparse_attn, hsa_sparse_attn_adaptive,
+                                      hsa_sparse_attn_workspace_size)
     n_q, H, d = q.shape
     n_pages = k.shape[1] // P
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
@@ -73,7 +75,11 @@ def _run(dtype, q, k, v, P, ws_bytes=None, scale=0.0):
     lse = torch.full((1, H, n_q), float("nan"), dtype=torch.float32, device="cuda:0")
     nbytes = hsa_sparse_attn_workspace_size(layer.cfg, n_q, 0, n_pages) if ws_bytes is None else ws_bytes
     ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0") if nbytes else None
-    hsa_sparse_attn(layer.cfg, up(q)[None], n_q, layer.pool, None, 0, None, 0, n_pages, o, lse=lse, ws=ws)
+    if adaptive:
+        hsa_sparse_attn_adaptive(layer.cfg, up(q)[None], n_q, layer.pool, None, 0, None, 0, n_pages, o,
+                                 lse=lse, tau_min=1.0, tau_max=1.0)
+    else:
+        hsa_sparse_attn(layer.cfg, up(q)[None], n_q, layer.pool, None, 0, None, 0, n_pages, o, lse=lse, ws=ws)
     torch.cuda.synchronize()
     return to_host(o)[0], to_host(lse)[0]
 
@@ -107,3 +113,16 @@ def test_a_query_with_no_weights(dtype, P, n_pages, scale):
     assert (o[none] == 0).all() and np.isneginf(lse[:, none]).all()
     assert_close("O_sp", o[~none], ref_o[~none], **(BF16_TOL if dtype == "bf16" else F32_TOL))
     np.testing.assert_allclose(lse[:, ~none], ref_lse[:, ~none], atol=2e-3 if dtype == "bf16" else 1e-4)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mask", ["first", "blocks"])
+def test_masked_blocks_of_the_tile_lists(dtype, mask):
+    # threshold 1: a block of masked keys (weight 0) is kept or not by the
+    # rounding of the running weight, and no key of it has a weight either way
+    say(f"[case] masked blocks {dtype} {mask}")
+    q, k, v, m = _inputs(np.random.default_rng(93), 2, 64, 300, 128, 5, mask, "inf")
+    o, lse = _run(dtype, q, k, v, 128, adaptive=True)
+    ref_o, ref_lse = _reference(q, k, v, m)
+    assert_close("O_sp", o, ref_o, **(BF16_TOL if dtype == "bf16" else F32_TOL))
+    np.testing.assert_allclose(lse, ref_lse, atol=2e-3 if dtype == "bf16" else 1e-4)

@@ -64,3 +64,31 @@ def _both(wl):
 def test_noalloc_matches_forward_twice_second_smaller():
     _both(BIG)
     _both(SMALL)
+
+
+def test_noalloc_f32_matches_forward():
+    # long lists on few query blocks, cut into pieces whose partials lie behind
+    # the selection in the static workspace, then short ones in the same bytes
+    import torch
+    from paper_2609_34606_amd import HsaLayer, hsa_forward_noalloc, hsa_forward_noalloc_bytes
+    from synth_inputs import make_case_torch
+    for wl in (SMALL.replace(dtype="f32", k_h=(1, 3, 7)),
+               SMALL.replace(dtype="f32", heads=2, k_h=(0, 2), head_dim=64, n_q=65, page_size=40)):
+        say(f"[case] noalloc f32 {wl}")
+        dev = make_case_torch(wl, "cuda:0")
+        q, k_h = dev["q"], [int(x) for x in dev["k_h"]]
+        B, n_q, H, d = q.shape
+        layer = HsaLayer(B, H, d, wl.page_size, q.dtype, q.device, k_pool=dev["k_pool"],
+                         v_pool=dev["v_pool"], page_table=dev["page_table"])
+        layer.fold(0, wl.n_pages)
+        need = hsa_forward_noalloc_bytes(layer.cfg, n_q, wl.n_cand, wl.n_cur, k_h, max(k_h))
+        assert 0 < need <= (128 << 20), need
+        o_a = layer.forward(q, wl.n_cand, wl.n_cur, k_h, g_lin=dev["g_lin"], g_sp=dev["g_sp"])
+        for _ in range(2):
+            o_b = torch.full_like(o_a, float("nan"))
+            hsa_forward_noalloc(layer.cfg, q, n_q, layer.pool, wl.n_cand, wl.n_cur, k_h, max(k_h),
+                                layer.kv_state, layer.k_state, layer.page_kmean, dev["g_lin"],
+                                dev["g_sp"], o_b)
+            torch.cuda.synchronize()
+            assert torch.isfinite(o_a).all()
+            assert torch.equal(o_a.view(torch.int32), o_b.view(torch.int32)), "outputs differ in some bits"
