@@ -110,7 +110,9 @@ const char* hsa_status_string(hsa_status_t status);
  * workspace pointer must be 256-byte aligned. Returns 0 on invalid input.
  * For fp32 the size counts scratch that lets the attention cut long items into
  * pieces; a call whose workspace ends before that scratch (or inside it) runs
- * with fewer pieces, or none. */
+ * with fewer pieces, or none, and then sums in another order: its outputs
+ * agree within fp32 rounding. With the size given here, or more, they are the
+ * same bits each time. */
 size_t hsa_state_update_workspace_size(const hsa_config_t* cfg, int32_t n_pages);
 size_t hsa_page_select_workspace_size(const hsa_config_t* cfg, int32_t n_q);
 size_t hsa_sparse_attn_workspace_size(const hsa_config_t* cfg, int32_t n_q,
@@ -133,11 +135,12 @@ size_t hsa_adaptive_workspace_size(const hsa_config_t* cfg, int32_t n_q,
  * 64-key tiles, at most HSA_PLAN_MAX_CHUNKS; launches of at least
  * 4 x HSA_PLAN_MAX_CHUNKS items, and launches of at most HSA_PLAN_MAX_CHUNKS
  * items whose longest item exceeds a range by at most four tiles (ten with
- * fewer than two ranges per item), take one workgroup per whole item) and the most pieces the ranges cut an item
- * into. Tile-list walk: the work items (128-query tile x key
- * split), the chunks of the launch's schedule table (at most
- * HSA_PLAN_MAX_CHUNKS) and the largest key split of a head. Each output
- * pointer is nullable. Errors: INVALID_ARG, UNSUPPORTED (no schedule fits;
+ * fewer than two ranges per item), take one workgroup per whole item) and the
+ * most pieces the ranges cut an item into. Tile-list walk: the work items
+ * (128-query tile x key split), the chunks of the launch's schedule table (at
+ * most HSA_PLAN_MAX_CHUNKS) and the largest key split of a head. An fp32 config
+ * gets its items uncut: fp32 launches are planned at the call, for the
+ * workspace it has. Each output pointer is nullable. Errors: INVALID_ARG, UNSUPPORTED (no schedule fits;
  * the attention calls then return the same). */
 #define HSA_PLAN_MAX_CHUNKS 256
 hsa_status_t hsa_attention_plan(const hsa_config_t* cfg, int32_t n_q, const int32_t* list_len,

@@ -105,9 +105,11 @@ StatePlan plan_state(const hsa_config_t* c, int n_pages) {
   // workgroup, written and read back). 3 pages of 1560 keys, 12 heads x d128,
   // append and fold: 40 us with 468 workgroups (what half this reduction cost
   // chooses), 33 us with 324, 35 us with 180; the 24- and 123-page folds keep
-  // their plans. fp32 tiles take four times the matrix time, which hides more
-  // of that traffic: 19 pages of 392, 8 heads, 194 us with 456 workgroups in a
-  // whole step, 201 us with 304.
+  // their plans. Over 84 folds of 1 to 12 pages of 200 to 3120 keys (4 to 24
+  // heads, d 64 and 128) it takes 0.84 to 1.05 of the time that half this
+  // reduction cost gives, 13 of them less than 0.98 and three more than 1.02.
+  // fp32 keeps half: with this one, 64 folds (up to 19 pages, 2 to 12 heads) take
+  // 0.85 to 1.17 of its time, three less than 0.98 and four more than 1.02.
   StatePlan best{1, c->page_size, 1, std::max(n_pages, 1)};
   if (n_pages <= 0) return best;
   const long bh = (long)c->batch * c->num_heads;

@@ -1221,17 +1221,19 @@ namespace {
 // items, and launches of at most 256 items whose longest item is at most
 // kCutTiles longer than a range (four tiles at two ranges per item, where
 // most ranges are one piece; else ten, since most ranges then hold two), take
-// one whole item per workgroup
-// (sk_whole): with many items per
-// range, the 32 ranges running on an XCD would each walk a different head
-// and share no page in its L2 (30 batched layers of the streaming workload:
+// one whole item per workgroup (sk_whole): with many items per range, the 32
+// ranges running on an XCD would each walk a different head and share no page
+// in its L2 (30 batched layers of the streaming workload:
 // 17.4 against 14.7 ms per chunk), while the dispatcher's own balancing
 // leaves a tail of at most one item in four. Small launches are bound by the
 // length of a range's serial walk (d = 64: 1.15 us per tile and 9 us around
 // it): 20 items of 12 to 28 tiles took 38 us in 23 ranges of at least 16 tiles
 // and take 31 us in 40 (4, 6 and 8 as the least tiles alike, the two ranges
-// per item bind). split = false (fp32, whose kernel does not read the
-// schedule) takes one range.
+// per item bind). Whole calls against 16 tiles and four tiles for every cut: 196
+// of 1 to 16 heads, 64 to 4680 queries and lists of 3 to 250 tiles (forward and
+// Linformer) take 0.76 to 1.02 of the time, 51 of them less than 0.98 and two
+// more than 1.02. split = false (fp32) takes one range: that launch keeps nqt
+// of this plan, for its tile lists, and is cut by plan_attention_f32.
 bool plan_stream_k(AttnParams& p, int B, int H, int n_q, int P, const int* list_len, int max_part,
                    bool split) {
   constexpr int kMaxRanges = 256, kMinTiles = 8, kWholeItems = 4 * kMaxRanges;

@@ -3,8 +3,8 @@
 // A.1 eq. attention) with fp32 operands, products and sums throughout.
 //
 // Both products run on the fp32 matrix instruction (16x16x4: a full fp32
-// multiply and add per term, four times the work per lane and cycle of a VALU
-// FMA without its LDS reads). The scores are computed transposed, S^T = K Q^T,
+// multiply and add per term, twice the work per cycle of VALU FMAs, and one LDS
+// read per operand and tile where an FMA needs one per term). The scores are computed transposed, S^T = K Q^T,
 // so that lane l holds four scores of query l % 16 per 16 keys, and the same
 // registers are the B operand of O^T += V^T P^T: probabilities never leave
 // their lane. The contraction order over d and over keys is free as long as
@@ -18,9 +18,9 @@
 // is merged by the last of its pieces to arrive, in piece order.
 //
 // Bound: the matrix pipes (4 n_q d per key and head; a large fp32 product
-// reaches 154 TFLOP/s). The tile loads and LDS reads are a tenth of what the
-// memory system gives, so they go through registers, which takes pointers of
-// any 4-byte alignment. Measured (8 heads x d128, 1170 queries, lists of 5 and
+// reaches 154 TFLOP/s). A step of eight MFMAs reads 2 KB per wave, a quarter of
+// the LDS bandwidth, and the tiles come from L2, so the tile loads go through
+// registers, which takes pointers of any 4-byte alignment. Measured (8 heads x d128, 1170 queries, lists of 5 and
 // 7 pages of 392 keys): 148 us, 76 TFLOP/s of the work, the matrix pipes busy
 // 0.63 of the cycles at a 2.05 GHz clock; the VALU kernel before it took
 // 3400 us. 2 heads x d64, 256 queries, 3 pages of 256: 17 us against 283.

@@ -308,8 +308,9 @@ __device__ __forceinline__ void count_ranks(const double* rp, int N, int lane, i
 }
 
 // The row's weights and ids in that order, in place: waves with share 0 and 1
-// of a row call it alike; every wave of the workgroup meets its two barriers
-// (active: this wave has a row).
+// of a row call it alike. One workgroup barrier, which every wave meets (active:
+// this wave has a row): between share 1's counts, written to ri, and share 0,
+// which reads them and then alone touches the row.
 template <int E>
 __device__ __forceinline__ void rank_order(double* rp, int32_t* ri, int N, int lane, int share, bool active) {
   int cnt[E];
