@@ -286,13 +286,16 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
         }
     }
     // online softmax against a reference maximum that moves only when a score
-    // exceeds it by more than 8 in log2 units (exact for any reference)
+    // exceeds it by more than 8 in log2 units (exact for any reference). Scores
+    // are compared and subtracted before they are scaled: the difference is
+    // small and exact where it matters, while a scaled score of 2^31 or more is
+    // rounded by more than the exponent of a float can hold.
     float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
                      fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-    if (__any(mx * c2 > m_run * c2 + 8.f)) {
+    if (__any((mx - m_run) * c2 > 8.f)) {
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const bool grow = mx * c2 > m_run * c2 + 8.f;
+      const bool grow = (mx - m_run) * c2 > 8.f;
       const float m_new = grow ? mx : m_run;
       const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c2);
       l_run *= alpha;
@@ -300,12 +303,11 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
       for (int m = 0; m < NM; ++m) acc[m] *= alpha;
       m_run = m_new;
     }
-    const float mc = m_run * c2;
     float pv[2][4];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) pv[kb][r] = __builtin_amdgcn_exp2f(fmaf(sc[kb][r], c2, -mc));
+      for (int r = 0; r < 4; ++r) pv[kb][r] = __builtin_amdgcn_exp2f((sc[kb][r] - m_run) * c2);
     l_run += ((pv[0][0] + pv[0][1]) + (pv[0][2] + pv[0][3])) + ((pv[1][0] + pv[1][1]) + (pv[1][2] + pv[1][3]));
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

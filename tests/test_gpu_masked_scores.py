@@ -126,3 +126,24 @@ def test_masked_blocks_of_the_tile_lists(dtype, mask):
     ref_o, ref_lse = _reference(q, k, v, m)
     assert_close("O_sp", o, ref_o, **(BF16_TOL if dtype == "bf16" else F32_TOL))
     np.testing.assert_allclose(lse, ref_lse, atol=2e-3 if dtype == "bf16" else 1e-4)
+
+
+@pytest.mark.parametrize("d,n_q,P,n_pages,ws_bytes", [(64, 70, 40, 9, None), (128, 70, 392, 5, None),
+                                                      (128, 70, 392, 5, 0)])
+def test_huge_fp32_scores(d, n_q, P, n_pages, ws_bytes):
+    # a few keys, in different tiles, streams and pieces, whose scores reach
+    # 1e20 and more: the largest takes all the weight (no two are near each
+    # other), whichever sign and order they have
+    say(f"[case] huge scores d={d} P={P} pages={n_pages} ws={ws_bytes}")
+    r = np.random.default_rng(94)
+    n = P * n_pages
+    q, k, v = (r.standard_normal(s).astype(np.float32) for s in ((n_q, 2, d), (2, n, d), (2, n, d)))
+    at = np.linspace(1, n - 2, 7).astype(int)
+    k[:, at, 0] = np.float32(1e21) * np.array([1.5, -4.0, 3.0, 8.0, -7.0, 0.25, -0.5], dtype=np.float32)
+    o, lse = _run("f32", q, k, v, P, ws_bytes)
+    s = np.einsum("qhd,hkd->hqk", q.astype(np.float64), k.astype(np.float64)) / np.sqrt(d)
+    best = s.argmax(-1)
+    assert (s.max(-1) > 1e15).all()
+    for h in range(2):
+        np.testing.assert_array_equal(o[:, h], v[h, best[h]])
+    np.testing.assert_allclose(lse, s.max(-1), rtol=1e-5)
