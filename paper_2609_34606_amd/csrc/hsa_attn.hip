@@ -1040,7 +1040,7 @@ __global__ __launch_bounds__(512, 1) void attn_pp_kernel(AttnParams p_arg) {
       // its loads and meets the barriers, in the same order: its matrix work
       // would cost power, and so shader clock, and take its SIMD's pipe from
       // the other wave (4680 queries: five of eight waves of every nineteenth
-      // tile; 8 layers in one launch 4.19 -> 4.05 ms, one layer 0.5 to 1%).
+      // tile; 8 layers in one launch 4.23 -> 4.06 ms, one layer 0.6 to 1.3%).
       // A branch of its own: tested inside the walk, the scores of the two
       // waves' paths meet and spill.
       for (int j = 0; j <= 2 * ntiles; ++j) {  // slot j

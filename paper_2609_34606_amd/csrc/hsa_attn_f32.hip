@@ -20,10 +20,11 @@
 // Bound: the matrix pipes (4 n_q d per key and head; a large fp32 product
 // reaches 154 TFLOP/s). A step of eight MFMAs reads 2 KB per wave, a quarter of
 // the LDS bandwidth, and the tiles come from L2, so the tile loads go through
-// registers, which takes pointers of any 4-byte alignment. Measured (8 heads x d128, 1170 queries, lists of 5 and
-// 7 pages of 392 keys): 148 us, 76 TFLOP/s of the work, the matrix pipes busy
-// 0.63 of the cycles at a 2.05 GHz clock; the VALU kernel before it took
-// 3400 us. 2 heads x d64, 256 queries, 3 pages of 256: 17 us against 283.
+// registers, which takes pointers of any 4-byte alignment. Measured (8 heads x
+// d128, 1170 queries, lists of 5 and 7 pages of 392 keys): 147 us, 77 TFLOP/s of
+// the work, the matrix pipes busy 0.62 of the cycles at a 2.12 GHz clock; the
+// VALU kernel before it took 3400 us. 2 heads x d64, 256 queries, 3 pages of
+// 256: 17 us against 283.
 #include <float.h>
 
 #include <algorithm>
