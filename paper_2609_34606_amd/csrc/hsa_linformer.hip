@@ -17,11 +17,12 @@
 // Bound: HBM (the pages; the projections come from L2). Under load a tile
 // takes about 5 us to arrive, so what counts is the bytes in flight per CU:
 // the data of the next two tiles is in registers or on its way while a tile is
-// computed, at four workgroups per CU. Measured, 48 pages of 1560 tokens x 12
-// heads x d128, rank 64 (460 MB): 112 us, 4.3 TB/s counting each page once;
-// one workgroup per page and head with both products, loading a tile and then
-// computing it, took 157 us, the same with one tile prefetched 132 us. Five
-// workgroups per CU spill registers: 140 us.
+// computed, at four workgroups per CU. Measured, 12 heads x d128, rank 64, pages
+// of 1560 tokens: 48 pages (460 MB) 118 us, 3.9 TB/s counting each page once,
+// and 123 pages 284 us, 4.1 TB/s; one workgroup per page and head with both
+// products, loading a tile and then computing it, took 157 and 288 us, the same
+// with one tile prefetched 132 us for the 48. Five workgroups per CU spill
+// registers: 140 us.
 #include <type_traits>
 
 #include "hsa_device.h"
@@ -62,15 +63,21 @@ __global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_
 
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Workgroup ids go round-robin to the 8 XCDs; each XCD takes consecutive
-  // items of a batch entry (head, product, page, part), so that the few
-  // projections it reads stay in its L2.
+  // Workgroup ids go round-robin to the 8 XCDs. Each XCD takes consecutive items
+  // (head, page, part) of the key product and then as many of the value
+  // product, so that the few projections it reads stay in its L2 and every XCD
+  // has the same work: a value tile, whose rows are 128-byte pieces, takes a
+  // sixth longer than a key tile. (head, product, page, part) gave XCDs two heads
+  // of one product and one of the other at 12 heads: 123 pages 304 us, now 284;
+  // 288 with both products in one workgroup.
   const int per = p.n_pages * p.parts, G = per * 2 * p.H;
   const int lin = (int)(blockIdx.y * gridDim.x + blockIdx.x), xcd = lin & 7;
-  const int item = xcd * (G >> 3) + min(xcd, G & 7) + (lin >> 3);
-  const int hk = item / per, pi = item % per / p.parts, part = item % p.parts;
-  const bool is_k = (hk & 1) == 0;
-  const int h = hk >> 1, b = blockIdx.z;
+  auto start = [&](int x) { return x * (G >> 3) + min(x, G & 7); };
+  const int s0 = start(xcd), s1 = start(xcd + 1), j = lin >> 3;
+  const int k0 = (s0 + 1) >> 1, v0 = s0 >> 1, nk = ((s1 + 1) >> 1) - k0;
+  const bool is_k = j < nk;
+  const int item = is_k ? k0 + j : v0 + (j - nk);
+  const int h = item / per, pi = item % per / p.parts, part = item % p.parts, b = blockIdx.z;
   const int page = p.first_page + pi;
   const int slot = clampi(p.page_table[(size_t)b * p.max_pages + page], 0, p.num_slots - 1);
   const size_t hb = (size_t)slot * p.H + h;
@@ -142,9 +149,16 @@ __global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_
     for (int n = 0; n < NE; ++n) g2lds16_hidden(src + e_off[n], sm.e[buf] + (wave * NE + n) * 1024);
   };
 
-  // one tile: registers -> LDS, the loads of the tile after next, products
+  // one tile: registers -> LDS, the loads of the tile after next, products.
+  // kPair: the loads of the next two tiles after the second of two; the two
+  // 128-byte pieces of a value row, which share a cache line, then meet in the
+  // cache. d = 64, rank 64, 16 heads, 96 pages of 1560: 175 -> 169 us; at d =
+  // 128, where a tile is twice as long, 24 pages took 47.5 -> 48.8 us.
+  constexpr bool kPair = !K && D == 64;
   constexpr int kLoadsX = K ? KPT : NV;
-  auto step = [&](int t0, u32x4 (&xr)[NV], int buf) {
+  auto step = [&](int t0, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    u32x4 (&xr)[NV] = x[buf];
     // valid tokens of this tile's window: [lo, hi), multiples of 8; the others
     // are zeros in one operand (keys; the projection of the values)
     const int lo = t0 - window(t0), hi = lo + min(kT, t_end - t0);
@@ -171,7 +185,7 @@ __global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_
       for (int n = 0; n < NV; ++n) *reinterpret_cast<u32x4*>(sm.x + ((wave * NV + n) * 64 + lane) * 16) = xr[n];
     }
     // this tile's projection has landed: only the next tile's data is later
-    if (t0 + kT < t_end) wait_vmcnt<kLoadsX>();
+    if ((!kPair || buf == 0) && t0 + kT < t_end) wait_vmcnt<kLoadsX>();
     else wait_vmcnt<0>();
     if constexpr (!K) {
       if (lo > 0 || hi < kT) {  // each lane clears what it loaded
@@ -185,7 +199,12 @@ __global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_
     }
     lds_barrier();
     if (t0 + kT < t_end) load_e(t0 + kT, buf ^ 1);
-    if (t0 + 2 * kT < t_end) load_x(t0 + 2 * kT, xr);
+    if constexpr (!kPair) {
+      if (t0 + 2 * kT < t_end) load_x(t0 + 2 * kT, xr);
+    } else if constexpr (buf == 1) {
+      if (t0 + kT < t_end) load_x(t0 + kT, x[0]);
+      if (t0 + 2 * kT < t_end) load_x(t0 + 2 * kT, x[1]);
+    }
     if (active) {
       // (opaque, so that the eight operand offsets are recomputed per tile
       // instead of held across the walk)
@@ -212,8 +231,8 @@ __global__ __launch_bounds__(256, R * D <= 64 * 128 ? 4 : 3) void compress_bf16_
     if (t_beg + kT < t_end) load_x(t_beg + kT, x[1]);
   }
   for (int t0 = t_beg; t0 < t_end; t0 += 2 * kT) {
-    step(t0, x[0], 0);
-    if (t0 + kT < t_end) step(t0 + kT, x[1], 1);
+    step(t0, std::integral_constant<int, 0>{});
+    if (t0 + kT < t_end) step(t0 + kT, std::integral_constant<int, 1>{});
   }
   };
   if (is_k) walk(std::true_type{});

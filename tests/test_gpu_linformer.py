@@ -112,6 +112,27 @@ def test_small_ragged_bf16(d, rank):
     _run(SMALL.replace(head_dim=d), rank=rank)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("P,n_pages,H", [(8, 3, 1), (64, 300, 1), (72, 2, 1), (136, 131, 2), (200, 1, 5),
+                                           (264, 90, 3), (392, 40, 7), (520, 3, 2)])
+def test_compression_over_tile_and_item_counts(P, n_pages, H, d):
+    # one to nine 64-token tiles per page, whole pages and parts of them, and
+    # item counts that the eight XCDs share unevenly: every page of a head is
+    # written once, by the right item
+    wl = SMALL.replace(page_size=P, n_cand=n_pages, n_cur=0, heads=H, k_h=(1,) * H, head_dim=d, n_q=64, seed=73)
+    say(f"[case] compression {wl}")
+    case = make_case(wl)
+    host = dict(k_pool=case.k_pool, v_pool=case.v_pool, page_table=case.page_table)
+    e_k, e_v = make_projections(wl, 32, "gaussian")
+    layer = _layer(wl, upload(case), e_k, e_v)
+    layer.ck.fill_(float("nan"))
+    layer.cv.fill_(float("nan"))
+    layer.compress(0, n_pages)
+    import torch
+    torch.cuda.synchronize()
+    _check_compressed(layer, host, e_k, e_v, wl, range(n_pages))
+
+
 @pytest.mark.parametrize("n_pages,parts", [(1, True), (86, False)])
 def test_compressed_pages_at_an_odd_element(n_pages, parts):
     # ck and cv one element past an aligned address: pages summed from parts
