@@ -233,7 +233,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     // splits are left (19 per thread at 4680 queries, d = 128), else the least
     // that holds them. Kernel times at one candidate list of 13 (before: eight
     // at a time, then one by one; ten always): 256 queries 5.4, 6.7, now 5.5
-    // us; 1560: 7.2, 6.6, 6.4; 3000: 7.3, 7.8, 6.9; 4680: 8.2, 8.1, 8.0.
+    // us; 1560: 7.2, 6.6, 6.4; 3000: 7.3, 7.8, 6.9; 4680: 8.2, 8.1, 8.0. The
+    // code here moves the ranking loop below: with 600 and 1500 candidates the
+    // three forms took 62 and 258, 66 and 275, 63 and 258 us; with == for <= in
+    // the tests, 69 and 296 us.
     double sacc = 0.0;
     int k = k0;
     auto sum = [&](auto batch) {
@@ -247,8 +250,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
       k += B;
     };
     while (k < k1) {
-      if (k1 - k == 1) sum(std::integral_constant<int, 1>{});
-      else if (k1 - k == 2) sum(std::integral_constant<int, 2>{});
+      if (k1 - k <= 1) sum(std::integral_constant<int, 1>{});
+      else if (k1 - k <= 2) sum(std::integral_constant<int, 2>{});
       else if (k1 - k <= 4) sum(std::integral_constant<int, 4>{});
       else sum(std::integral_constant<int, 10>{});
     }
