@@ -259,7 +259,9 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
       f[0] = ld4s(vt + v_at(16 * m + l16, 4 * kb + g));
       f[1] = ld4s(vt + v_at(16 * m + 16 + l16, 4 * kb + g));
     };
-    f32x4 sc[2] = {f32x4{0}, f32x4{0}};
+    // Two partial sums per score, each over half of d: the instruction rounds
+    // after every term, and one chain over d = 128 leaves twice the error.
+    f32x4 sc[2] = {f32x4{0}, f32x4{0}}, sd[2] = {f32x4{0}, f32x4{0}};
 #pragma unroll
     for (int c = 0; c < kAhead; ++c) kop(c, a[c]);
 #pragma unroll
@@ -268,11 +270,14 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void attn_f32_kernel(
       if (c + kAhead < NC) kop(c + kAhead, a[c % kAhead]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        sc[0] = mfma16(f[0][e], qf[c][e], sc[0]);
-        sc[1] = mfma16(f[1][e], qf[c][e], sc[1]);
+        f32x4 (&t)[2] = c < NC / 2 ? sc : sd;
+        t[0] = mfma16(f[0][e], qf[c][e], t[0]);
+        t[1] = mfma16(f[1][e], qf[c][e], t[1]);
       }
     }
     pipeline_reads<NC, kAhead>();
+    sc[0] += sd[0];
+    sc[1] += sd[1];
     __builtin_amdgcn_sched_barrier(0);
     f32x4 w[kAhead][2];
 #pragma unroll

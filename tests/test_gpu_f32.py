@@ -161,3 +161,43 @@ def test_infinite_value_stays_in_its_page_and_dimension():
     assert np.isposinf(got[0, :, 1, 5]).all()
     got[0, :, 1, 5] = 0.0
     assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("adaptive", [False, True])
+def test_scores_round_less_than_one_chain_over_d(d, adaptive):
+    # Terms of one sign make the partial sums grow along d, so each rounding
+    # counts. Key 0 has all the weight, and the LSE is its score: its error
+    # against 64 bits must stay below what one fp32 chain over d shows for the
+    # same numbers (emulated: the product of two floats is exact in 64 bits, the
+    # sum is rounded to 32). Measured on that emulation, in units of 2^-24: one
+    # chain 2.0 (d = 64) and 3.0, two halves 1.2 and 1.5; the LSE's scaling and
+    # addition round at most three times more (0.3 each, added in squares).
+    import torch
+    from paper_2609_34606_amd import HsaLayer, hsa_sparse_attn, hsa_sparse_attn_adaptive
+    say(f"[case] f32 score rounding d={d} adaptive={adaptive}")
+    H, n_q, P = 4, 256, 8
+    r = np.random.default_rng(75)
+    q = np.abs(r.standard_normal((n_q, H, d))).astype(np.float32)
+    k = -np.abs(r.standard_normal((1, H, P, d))).astype(np.float32)
+    k[:, :, 0] *= -1
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    layer = HsaLayer(1, H, d, P, torch.float32, "cuda:0", k_pool=up(k),
+                     v_pool=up(np.ones((1, H, d, P), dtype=np.float32)),
+                     page_table=torch.zeros((1, 1), dtype=torch.int32, device="cuda:0"), sm_scale=1.0)
+    o = torch.zeros((1, n_q, H, d), dtype=torch.float32, device="cuda:0")
+    lse = torch.zeros((1, H, n_q), dtype=torch.float32, device="cuda:0")
+    if adaptive:
+        hsa_sparse_attn_adaptive(layer.cfg, up(q)[None], n_q, layer.pool, None, 0, None, 0, 1, o, lse=lse,
+                                 tau_min=1.0, tau_max=1.0)
+    else:
+        hsa_sparse_attn(layer.cfg, up(q)[None], n_q, layer.pool, None, 0, None, 0, 1, o, lse=lse)
+    torch.cuda.synchronize()
+    q64, k64 = q.astype(np.float64), k[0, :, 0].astype(np.float64)
+    ref = np.einsum("qhd,hd->hq", q64, k64)
+    assert ref.min() > 8  # the other keys' scores are as far below zero
+    chain = np.zeros((H, n_q), dtype=np.float32)
+    for i in range(d):
+        chain = (chain.astype(np.float64) + q64[:, :, i].T * k64[:, None, i]).astype(np.float32)
+    rms = lambda x: float(np.sqrt((((x - ref) / ref) ** 2).mean()))
+    assert rms(to_host(lse)[0]) <= 0.8 * rms(chain)
