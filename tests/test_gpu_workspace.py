@@ -72,9 +72,11 @@ class _Call:
                     retrieval=hsa.hsa_retrieval_workspace_size)[kind]
         self.full = size(self.layer.cfg, wl.n_q, self.k_max, wl.n_cur)
 
-    def run(self, ws):
+    def launch(self, ws):
+        """Enqueues the call: (o, sel, the chosen chunk or None)."""
         import torch
         L, wl, dev, hsa = self.layer, self.wl, self.dev, self.hsa
+        chunk = None
         o = torch.full_like(dev["q"], float("nan"))
         sel = torch.full((wl.batch, wl.heads, self.k_max), -7, dtype=torch.int32, device="cuda:0")
         head = (L.cfg, dev["q"], wl.n_q, L.pool)
@@ -93,8 +95,13 @@ class _Call:
             chunk = torch.full((wl.batch,), -7, dtype=torch.int32, device="cuda:0")
             hsa.hsa_forward_retrieval(*head, pe, ce, ce.shape[2], ce.shape[1], cf, wl.n_cand, wl.n_cur,
                                       self.k_h, self.k_max, *state, *tail, chunk_out=chunk, sel_out=sel, ws=ws)
-            assert chunk.tolist() == [0]
+        return o, sel, chunk
+
+    def run(self, ws):
+        import torch
+        o, sel, chunk = self.launch(ws)
         torch.cuda.synchronize()
+        assert chunk is None or chunk.tolist() == [0]
         return o, to_host(sel)
 
     def reference(self):
@@ -145,3 +152,28 @@ def test_contents_of_the_workspace_do_not_matter(kind, dtype, d):
     for b, s in runs:
         assert torch.equal(a.view(bits), b.view(bits)), "outputs differ in some bits"
         np.testing.assert_array_equal(s, sel)
+
+
+@pytest.mark.parametrize("kind", ["forward", "adaptive", "linformer", "retrieval"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_captured_calls_replay(kind, dtype):
+    # a captured call clears its own arrival counters: every replay gives the
+    # eager call's bits, whatever is left in the workspace in between
+    import torch
+    wl = WL.replace(dtype=dtype)
+    say(f"[case] captured {kind} {wl}")
+    call = _Call(kind, wl)
+    bits = torch.int16 if dtype == "bf16" else torch.int32
+    ws = torch.zeros(call.full, dtype=torch.uint8, device="cuda:0")
+    ref, sel = call.run(ws)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        o, s, _ = call.launch(ws)
+    for fill in (255, 0, 1, None):
+        if fill is not None:
+            ws.fill_(fill)
+        call.run(torch.full_like(ws, 255))  # eager work between the replays
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o.view(bits), ref.view(bits)), f"replay after {fill} differs in some bits"
+        np.testing.assert_array_equal(to_host(s), sel)
